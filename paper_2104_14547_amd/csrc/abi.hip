@@ -715,7 +715,11 @@ int nurbs_surface_uv_ws_bytes(nurbs_ctx* ctx, int B, int p, int q, int nu_c, int
     if (!out) return fail(ctx, NURBS_EINVAL, "out is NULL");
     if (grad_mask & ~NURBS_GRAD_ALL) return fail(ctx, NURBS_EINVAL, "unknown gradient bits");
     if (grad_mask == 0) *out = (ctx->flags & NURBS_VALIDATE) ? kWsHeader : 0;
-    else *out = uv_layout(B, p, q, nu_c, nv_c).total;
+    else {
+        *out = uv_layout(B, p, q, nu_c, nv_c).total;
+        UvSort so;
+        if (uv_sort_plan(B, p, q, nu_c, nv_c, npts, kWsHeader, &so)) *out = std::max(*out, so.total);
+    }
     return NURBS_OK;
 }
 
@@ -751,6 +755,15 @@ int nurbs_surface_uv_bwd(nurbs_ctx* ctx, int B, int p, int q, int nu_c, int nv_c
     if (npts > 0 && (!uv || !grad_pts)) return fail(ctx, NURBS_EINVAL, "NULL uv or grad_pts");
     const UvArgs a = uv_args(ctx, B, p, q, nu_c, nv_c, npts, ctrl, w, ku, kv, uv, uv_shared, ws);
     char* wb = reinterpret_cast<char*>(ws);
+    // pairs ordered by cell wherever that path takes the shape and the
+    // workspace holds its tables; a workspace sized for fewer pairs still
+    // holds the accumulators of the atomic path
+    UvSort so;
+    if (uv_sort_plan(B, p, q, nu_c, nv_c, npts, kWsHeader, &so) && ws_bytes >= so.total) {
+        hipError_t e = launch_uv_bwd_sorted(a, so, wb, reinterpret_cast<hipStream_t>(stream), grad_pts, grad_mask,
+                                            grad_ctrl, grad_w, grad_ku, grad_kv);
+        return e ? hip_fail(ctx, e, "launch uv backward") : NURBS_OK;
+    }
     hipError_t e = launch_uv_bwd(a, reinterpret_cast<hipStream_t>(stream), grad_pts, grad_mask,
                                  reinterpret_cast<unsigned*>(wb + l.maxbits),
                                  reinterpret_cast<unsigned long long*>(wb + l.acc), grad_ctrl, grad_w, grad_ku, grad_kv);

@@ -246,6 +246,71 @@ __device__ __forceinline__ void basis_knot_adjoint(const float* __restrict__ U, 
 }
 
 // ---------------------------------------------------------------------------
+// the recursion on one span, from its knot window
+// ---------------------------------------------------------------------------
+// On span k only the windows [U_{k-d+m}, U_{k+m}], 1 <= m <= d, of level d
+// carry a non-zero value, and every one of them contains [U_k, U_{k+1}]:
+//   N_{k-d+m}^d   += (x - lo) / (hi - lo) N_{k-d+m}^{d-1},
+//   N_{k-d+m-1}^d += (hi - x) / (hi - lo) N_{k-d+m}^{d-1}.
+// So alpha of one function and beta of its left neighbour share a
+// denominator, D(D+1)/2 reciprocals serve a whole span, and with
+// s = N^{d-1} / (hi - lo) and the adjoints a, b of the two sums the reverse
+// step is d lo += s (b - a) (hi - x) / (hi - lo), d hi += s (b - a) (x - lo)
+// / (hi - lo), d N^{d-1} = (a (x - lo) + b (hi - x)) / (hi - lo).
+// K[t] = U_{k-D+1+t}, t = 0..2D-1; level d's window m is entry
+// d(d-1)/2 + m - 1 of inv and s.
+constexpr int tri(int d, int m) { return d * (d - 1) / 2 + m - 1; }
+
+template <int D>
+__device__ __forceinline__ void span_inv(const float* K, float* inv) {
+#pragma unroll
+    for (int d = 1; d <= D; ++d)
+#pragma unroll
+        for (int m = 1; m <= d; ++m) inv[tri(d, m)] = recip(K[D - 1 + m] - K[D - 1 - d + m]);
+}
+
+template <int D>
+__device__ __forceinline__ void span_basis(const float* K, const float* inv, float x, float* N, float* s) {
+    N[0] = 1.0f;
+#pragma unroll
+    for (int d = 1; d <= D; ++d) {
+        float carry = 0.0f;
+#pragma unroll
+        for (int m = 1; m <= d; ++m) {
+            const float t = N[m - 1] * inv[tri(d, m)];
+            s[tri(d, m)] = t;
+            N[m - 1] = __builtin_fmaf(K[D - 1 + m] - x, t, carry);
+            carry = (x - K[D - 1 - d + m]) * t;
+        }
+        N[d] = carry;
+    }
+}
+
+// gK[t] = d/dK[t] of sum_r e[r] N_{k-D+r}(x); the outermost knots U_{k-D} and
+// U_{k+D+1} of the functions' supports do not enter on span k.
+template <int D>
+__device__ __forceinline__ void span_adjoint(const float* K, const float* inv, float x, const float* s,
+                                             const float* e, float* gK) {
+    float A[D + 1];
+#pragma unroll
+    for (int r = 0; r <= D; ++r) A[r] = e[r];
+#pragma unroll
+    for (int t = 0; t < 2 * D; ++t) gK[t] = 0.0f;
+#pragma unroll
+    for (int d = D; d >= 1; --d)
+#pragma unroll
+        for (int m = 1; m <= d; ++m) {
+            const int lo = D - 1 - d + m, hi = D - 1 + m;
+            const float xl = x - K[lo], hx = K[hi] - x;
+            const float a = A[m], b = A[m - 1];
+            const float c = s[tri(d, m)] * inv[tri(d, m)] * (b - a);
+            gK[lo] = __builtin_fmaf(c, hx, gK[lo]);
+            gK[hi] = __builtin_fmaf(c, xl, gK[hi]);
+            A[m - 1] = inv[tri(d, m)] * __builtin_fmaf(a, xl, b * hx);
+        }
+}
+
+// ---------------------------------------------------------------------------
 // one surface's arrays
 // ---------------------------------------------------------------------------
 struct Surf {

@@ -1,0 +1,583 @@
+// Backward of surfaces at scattered parameter pairs, over pairs ordered by
+// cell.  A cell is a pair of knot spans: its pairs touch the same
+// (p+1)(q+1) control points and the same 2p + 2q knots, so their terms are
+// summed in registers, and a control point's gradient is the sum over the
+// (p+1)(q+1) cells that touch it.  With h = g / W (h_w = -(S - c).g / W, c a
+// control point of the cell) a cell needs only
+//   M_rh = sum_k Nu_r(k) Nv_h(k) h(k)   (4 values per control point)
+//   dP = w M_xyz,   dw = (P - c) . M_xyz + M_w  (eqs. NURBSuDerivative4, 5)
+// and the knot adjoints of its pairs (eq. NURBSvDerivative6, Sec. 3.2.1).
+// The frame c keeps the two parts of dw as small as the cell.
+//
+//   k_uv_hist   each pair's cell; pairs per (chunk, cell)
+//   k_uv_scan   prefix over chunks, then over cells; cells cut into items of
+//               at most `seg` pairs
+//   k_uv_order  stable order by cell: pair indices, one wave per chunk
+//   k_uv_cell   one wave per item: sums of its pairs, in FP64
+//   k_uv_sum    sums over items in a fixed order, in FP64
+//
+// The order within a cell is the input's, so every sum has a fixed order and
+// results are bitwise reproducible, with no atomics on results and no pass to
+// find a fixed-point scale.  What bounds it: k_uv_cell's per-pair VALU work.
+// A bicubic pair costs 64 multiply-adds in FP64 for M, one per lane (lane o
+// owns output o and reads the wave's 64 pairs from LDS, two b128 reads per
+// four pairs), against 80 64-bit LDS atomics, as many conversions and a
+// second evaluation of every term on the atomic path.  Measured, backward
+// alone: 64 bicubic 16 x 16 surfaces x 65536 pairs 255 us (atomic path 600 us);
+// one surface of degree (4, 5), 48 x 41 net, 50001 pairs 122 us (1.70 ms, its
+// accumulators did not fit in LDS).  Largest error against 64 bits 1.6e-7 and
+// 2.3e-7 (5.8e-7 and 5.9e-7).
+#include "device.hpp"
+#include "launch.hpp"
+#include "../../include/nurbsdiff.h"
+
+#include <algorithm>
+
+namespace nd {
+namespace {
+
+// The (tables of the) group's surfaces: index b within the group.
+struct SortPtrs {
+    unsigned* hist;        // [group][nchunk][cells]: pairs, then their prefix over chunks
+    int* cell_start;       // [group][cells + 1]
+    int* item_start;       // [group][cells + 1]
+    int* item_cell;        // [group][items]
+    unsigned* order;       // [group][npts]
+    unsigned short* cell;  // [group][npts]
+    double* slots;         // [group][items][slot]
+};
+
+// --------------------------------------------------------------------------
+// ordering
+// --------------------------------------------------------------------------
+__global__ void __launch_bounds__(kWG) k_uv_hist(UvArgs a, UvSort s, SortPtrs t, int b0) {
+    extern __shared__ unsigned hist[];
+    __shared__ float lku[kWG], lkv[kWG];
+    const int g = blockIdx.y, b = b0 + g, tid = threadIdx.x;
+    const int nU = a.nu_c + a.p + 1, nV = a.nv_c + a.q + 1;
+    const float* gku = a.ku + (size_t)b * nU;
+    const float* gkv = a.kv + (size_t)b * nV;
+    for (int i = tid; i < nU; i += kWG) lku[i] = gku[i];
+    for (int i = tid; i < nV; i += kWG) lkv[i] = gkv[i];
+    for (int i = tid; i < s.cells; i += kWG) hist[i] = 0u;
+    __syncthreads();
+    const float* uv = a.uv + (a.uv_shared ? 0 : (size_t)b * a.npts * 2);
+    const int k0 = blockIdx.x * s.chunk, k1 = min(a.npts, k0 + s.chunk);
+    if (a.err) {
+        bool bad_k = false, bad_w = false, bad_d = false;
+        if (blockIdx.x == 0) {
+            for (int i = tid; i + 1 < nU; i += kWG) bad_k |= !(lku[i] <= lku[i + 1]);
+            for (int i = tid; i + 1 < nV; i += kWG) bad_k |= !(lkv[i] <= lkv[i + 1]);
+            if (tid == 0)
+                bad_k |= !(lku[a.p] < lku[a.p + 1]) || !(lku[a.nu_c - 1] < lku[a.nu_c]) ||
+                         !(lkv[a.q] < lkv[a.q + 1]) || !(lkv[a.nv_c - 1] < lkv[a.nv_c]);
+            const float* w = a.w + (size_t)b * a.nu_c * a.nv_c;
+            for (int i = tid; i < a.nu_c * a.nv_c; i += kWG) bad_w |= !(w[i] > 0.f);
+        }
+        for (int k = k0 + tid; k < k1; k += kWG) {
+            const float u = uv[2 * (size_t)k], v = uv[2 * (size_t)k + 1];
+            bad_d |= !(u >= lku[a.p] && u <= lku[a.nu_c] && v >= lkv[a.q] && v <= lkv[a.nv_c]);
+        }
+        if (bad_k) atomicCAS(a.err, 0, NURBS_EKNOTS);
+        if (bad_w) atomicCAS(a.err, 0, NURBS_EWEIGHTS);
+        if (bad_d) atomicCAS(a.err, 0, NURBS_EDOMAIN);
+    }
+    for (int k = k0 + tid; k < k1; k += kWG) {
+        const float2 x = *reinterpret_cast<const float2*>(uv + 2 * (size_t)k);
+        const int ku = find_span(lku, a.p, a.nu_c - 1, clamp_param(lku, a.p, a.nu_c - 1, x.x));
+        const int kv = find_span(lkv, a.q, a.nv_c - 1, clamp_param(lkv, a.q, a.nv_c - 1, x.y));
+        const int c = (ku - a.p) * s.ncv + (kv - a.q);
+        t.cell[(size_t)g * a.npts + k] = (unsigned short)c;
+        atomicAdd(hist + c, 1u);
+    }
+    __syncthreads();
+    unsigned* o = t.hist + ((size_t)g * s.nchunk + blockIdx.x) * s.cells;
+    for (int i = tid; i < s.cells; i += kWG) o[i] = hist[i];
+}
+
+// One workgroup per surface.  cells <= kUvCellsMax = 4 kScanWG.
+constexpr int kScanWG = 1024;
+__global__ void __launch_bounds__(kScanWG) k_uv_scan(UvSort s, SortPtrs t) {
+    __shared__ int tot[kUvCellsMax];
+    __shared__ int2 wsum[kScanWG / kWave];
+    const int g = blockIdx.x, tid = threadIdx.x;
+    unsigned* h = t.hist + (size_t)g * s.nchunk * s.cells;
+    for (int c = tid; c < kUvCellsMax; c += kScanWG) {
+        unsigned run = 0;
+        if (c < s.cells) {
+            constexpr int kU = 8;
+            for (int j0 = 0; j0 < s.nchunk; j0 += kU) {
+                unsigned v[kU];
+#pragma unroll
+                for (int u = 0; u < kU; ++u) v[u] = j0 + u < s.nchunk ? h[(size_t)(j0 + u) * s.cells + c] : 0u;
+#pragma unroll
+                for (int u = 0; u < kU; ++u)
+                    if (j0 + u < s.nchunk) {
+                        h[(size_t)(j0 + u) * s.cells + c] = run;
+                        run += v[u];
+                    }
+            }
+        }
+        tot[c] = (int)run;
+    }
+    __syncthreads();
+    // exclusive prefix of (pairs, items) over the cells, four per thread
+    constexpr int kPer = kUvCellsMax / kScanWG;
+    int n[kPer], sum = 0, isum = 0;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        n[i] = tot[tid * kPer + i];
+        sum += n[i];
+        isum += (n[i] + s.seg - 1) / s.seg;
+    }
+    int x = sum, y = isum;
+    for (int d = 1; d < kWave; d <<= 1) {
+        const int xo = __shfl_up(x, d), yo = __shfl_up(y, d);
+        if (lane_id() >= d) {
+            x += xo;
+            y += yo;
+        }
+    }
+    if (lane_id() == kWave - 1) wsum[tid / kWave] = make_int2(x, y);
+    __syncthreads();
+    int at = x - sum, it = y - isum;
+    for (int w = 0; w < tid / kWave; ++w) {
+        at += wsum[w].x;
+        it += wsum[w].y;
+    }
+    int* cs = t.cell_start + (size_t)g * (s.cells + 1);
+    int* is = t.item_start + (size_t)g * (s.cells + 1);
+    int* ic = t.item_cell + (size_t)g * s.items;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        const int c = tid * kPer + i;
+        if (c <= s.cells) {
+            cs[c] = at;
+            is[c] = it;
+        }
+        const int ni = (n[i] + s.seg - 1) / s.seg;
+        for (int j = 0; j < ni; ++j) ic[it + j] = c;
+        at += n[i];
+        it += ni;
+    }
+    if (tid == kScanWG - 1 && s.cells == kUvCellsMax) {
+        cs[s.cells] = at;
+        is[s.cells] = it;
+    }
+}
+
+// One wave per chunk: its pairs in input order, 64 at a time.  The lanes of
+// one cell find each other by ballots over the bits of the cell index, the
+// cell's counter in LDS gives the first position.
+__global__ void __launch_bounds__(kWave) k_uv_order(UvArgs a, UvSort s, SortPtrs t, int bits) {
+    extern __shared__ unsigned next[];
+    const int g = blockIdx.y, lane = lane_id();
+    const unsigned* h = t.hist + ((size_t)g * s.nchunk + blockIdx.x) * s.cells;
+    const int* cs = t.cell_start + (size_t)g * (s.cells + 1);
+    for (int c = lane; c < s.cells; c += kWave) next[c] = h[c] + (unsigned)cs[c];
+    wave_lds_sync();
+    const unsigned short* cell = t.cell + (size_t)g * a.npts;
+    unsigned* order = t.order + (size_t)g * a.npts;
+    const int k0 = blockIdx.x * s.chunk, k1 = min(a.npts, k0 + s.chunk);
+    for (int k = k0; k < k1; k += kWave) {
+        const bool act = k + lane < k1;
+        const int c = act ? (int)cell[k + lane] : 0;
+        unsigned long long m = __ballot(act);
+        for (int i = 0; i < bits; ++i) {
+            const bool bit = (c >> i) & 1;
+            const unsigned long long v = __ballot(bit);
+            m &= bit ? v : ~v;
+        }
+        const int rank = __popcll(m & ((1ull << lane) - 1ull));
+        const unsigned base = next[c];
+        wave_lds_sync();
+        if (act && rank == 0) next[c] = base + (unsigned)__popcll(m);
+        wave_lds_sync();
+        if (act) order[base + rank] = (unsigned)(k + lane);
+    }
+}
+
+// --------------------------------------------------------------------------
+// the pairs of an item
+// --------------------------------------------------------------------------
+template <int DM>
+struct SpanTab {
+    float K[2 * DM];                 // the span's knot window
+    float inv[DM * (DM + 1) / 2];    // its reciprocals
+};
+
+#define ND_BY_DEGREE(d, BODY)                                                             \
+    switch (d) {                                                                          \
+        case 1: if constexpr (1 <= DM) { constexpr int D = 1; BODY } break;               \
+        case 2: if constexpr (2 <= DM) { constexpr int D = 2; BODY } break;               \
+        case 3: if constexpr (3 <= DM) { constexpr int D = 3; BODY } break;               \
+        case 4: if constexpr (4 <= DM) { constexpr int D = 4; BODY } break;               \
+        case 5: if constexpr (5 <= DM) { constexpr int D = 5; BODY } break;               \
+        case 6: if constexpr (6 <= DM) { constexpr int D = 6; BODY } break;               \
+        case 7: if constexpr (7 <= DM) { constexpr int D = 7; BODY } break;               \
+        default: break;                                                                   \
+    }
+
+template <int DM>
+__device__ __forceinline__ void span_load(const float* __restrict__ U, int k, int d, SpanTab<DM>& t) {
+#pragma unroll
+    for (int i = 0; i < 2 * DM; ++i) t.K[i] = i < 2 * d ? uniform_f(U[k - d + 1 + i]) : 0.f;
+    ND_BY_DEGREE(d, span_inv<D>(t.K, t.inv);)
+#pragma unroll
+    for (int i = 0; i < DM * (DM + 1) / 2; ++i) t.inv[i] = i < d * (d + 1) / 2 ? uniform_f(t.inv[i]) : 0.f;
+}
+
+template <int DM>
+__device__ __forceinline__ void span_basis_rt(const SpanTab<DM>& t, int d, float x, float N[DM + 1],
+                                              float s[DM * (DM + 1) / 2]) {
+#pragma unroll
+    for (int r = 0; r <= DM; ++r) N[r] = 0.f;
+    ND_BY_DEGREE(d, span_basis<D>(t.K, t.inv, x, N, s);)
+}
+
+template <int DM>
+__device__ __forceinline__ void span_adjoint_rt(const SpanTab<DM>& t, int d, float x,
+                                                const float s[DM * (DM + 1) / 2], const float e[DM + 1],
+                                                float g[2 * DM]) {
+#pragma unroll
+    for (int i = 0; i < 2 * DM; ++i) g[i] = 0.f;
+    ND_BY_DEGREE(d, span_adjoint<D>(t.K, t.inv, x, s, e, g);)
+}
+
+// Row pitch of the 64 pairs' values in LDS: 16-byte rows, 4 banks apart, so
+// the 16 rows that a b128 read touches lie in different banks.
+constexpr int kPitch = kWave + 4;
+
+template <int PM, int QM>
+struct CellLds {
+    float4 patch[(PM + 1) * (QM + 1)];  // ((P - c) w, w) of the cell's control points
+    float nu[PM + 1][kPitch];
+    float tv[4 * (QM + 1)][kPitch];     // Nv_h h_c
+};
+
+// Sum of v over the wave's lanes for each of n <= 16 values per lane, in a
+// fixed order; lane 4t returns value t's sum.  buf: n rows of kRed doubles.
+constexpr int kRed = kWave + 2;
+template <int N>
+__device__ __forceinline__ double wave_sums(double* buf, const double (&v)[N], int n) {
+    static_assert(N <= kWave / 4, "four lanes to a value");
+    const int lane = lane_id();
+    wave_lds_sync();
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+        if (i < n) buf[i * kRed + lane] = v[i];
+    wave_lds_sync();
+    double x = 0.0;
+    const int row = min(lane >> 2, n - 1);
+#pragma unroll
+    for (int j = 0; j < kWave / 4; ++j) x += buf[row * kRed + (lane & 3) * (kWave / 4) + j];
+    x += __shfl_xor(x, 1);
+    x += __shfl_xor(x, 2);
+    wave_lds_sync();
+    return x;
+}
+
+template <int PM, int QM>
+__global__ void __launch_bounds__(kWG) k_uv_cell(UvArgs a, UvSort s, SortPtrs t, int b0,
+                                                const float* __restrict__ gpts, unsigned mask) {
+    __shared__ CellLds<PM, QM> lds_all[kWavesPerWG];
+    static_assert(sizeof(CellLds<PM, QM>) - sizeof(float4) * (PM + 1) * (QM + 1) >=
+                      sizeof(double) * kRed * 2 * (PM > QM ? PM : QM),
+                  "the knot sums reuse the pairs' rows");
+    CellLds<PM, QM>& L = lds_all[threadIdx.x / kWave];
+    const int g = blockIdx.y, b = b0 + g, lane = lane_id();
+    const int item = uniform((int)(blockIdx.x * kWavesPerWG + threadIdx.x / kWave));
+    const int* cs = t.cell_start + (size_t)g * (s.cells + 1);
+    const int* is = t.item_start + (size_t)g * (s.cells + 1);
+    if (item >= is[s.cells]) return;
+    const int p = a.p, q = a.q;
+    const int cell = uniform(t.item_cell[(size_t)g * s.items + item]);
+    const int cu = cell / s.ncv, cv = cell - cu * s.ncv;
+    const int s0 = uniform(cs[cell]) + (item - uniform(is[cell])) * s.seg;
+    const int s1 = min(s0 + s.seg, uniform(cs[cell + 1]));
+
+    SpanTab<PM> tu;
+    SpanTab<QM> tv;
+    const int nU = a.nu_c + p + 1, nV = a.nv_c + q + 1;
+    span_load<PM>(a.ku + (size_t)b * nU, cu + p, p, tu);
+    span_load<QM>(a.kv + (size_t)b * nV, cv + q, q, tv);
+    // domain ends, for the clamp
+    const float ulo = uniform_f(a.ku[(size_t)b * nU + p]), uhi = uniform_f(a.ku[(size_t)b * nU + a.nu_c]);
+    const float vlo = uniform_f(a.kv[(size_t)b * nV + q]), vhi = uniform_f(a.kv[(size_t)b * nV + a.nv_c]);
+
+    // the cell's control points in its frame; lane i < (p+1)(q+1) holds point i
+    const int npatch = (p + 1) * (q + 1);
+    const size_t cp0 = (size_t)b * a.nu_c * a.nv_c;
+    float4 pc;  // (P - c, w) of control point min(lane, npatch - 1)
+    {
+        const int mid = (cu + (p >> 1)) * a.nv_c + cv + (q >> 1);
+        const float* c = a.ctrl + 3 * (cp0 + mid);
+        const int i = min(lane, npatch - 1), r = i / (q + 1), h = i - r * (q + 1);
+        const size_t ij = cp0 + (size_t)(cu + r) * a.nv_c + cv + h;
+        const float* P = a.ctrl + 3 * ij;
+        pc = make_float4(P[0] - c[0], P[1] - c[1], P[2] - c[2], a.w[ij]);
+        if (lane < npatch) L.patch[lane] = make_float4(pc.x * pc.w, pc.y * pc.w, pc.z * pc.w, pc.w);
+    }
+    wave_lds_sync();
+
+    const bool want_pw = (mask & (NURBS_GRAD_CTRL | NURBS_GRAD_W)) != 0;
+    const bool want_ku = (mask & NURBS_GRAD_KU) != 0, want_kv = (mask & NURBS_GRAD_KV) != 0;
+    const float* uvb = a.uv + (a.uv_shared ? 0 : (size_t)b * a.npts * 2);
+    const float* gb = gpts + (size_t)b * a.npts * 3;
+    const unsigned* order = t.order + (size_t)g * a.npts;
+
+    // outputs o = (r (q+1) + h) 4 + c owned by this lane
+    constexpr int kOwn = ((PM + 1) * (QM + 1) * 4 + kWave - 1) / kWave;
+    double acc[kOwn];
+    int row_u[kOwn], row_v[kOwn];
+#pragma unroll
+    for (int m = 0; m < kOwn; ++m) {
+        const int o = min(lane + m * kWave, 4 * npatch - 1), rh = o >> 2;
+        row_u[m] = rh / (q + 1);
+        row_v[m] = (rh - row_u[m] * (q + 1)) * 4 + (o & 3);
+        acc[m] = 0.0;
+    }
+    double sku[2 * PM], skv[2 * QM];
+#pragma unroll
+    for (int i = 0; i < 2 * PM; ++i) sku[i] = 0.0;
+#pragma unroll
+    for (int i = 0; i < 2 * QM; ++i) skv[i] = 0.0;
+
+    for (int k = s0; k < s1; k += kWave) {
+        const bool act = k + lane < s1;
+        const size_t id = order[min(k + lane, s1 - 1)];
+        const float2 x = *reinterpret_cast<const float2*>(uvb + 2 * id);
+        const float u = fminf(fmaxf(x.x, ulo), uhi), v = fminf(fmaxf(x.y, vlo), vhi);
+        const float g0 = act ? gb[3 * id] : 0.f, g1 = act ? gb[3 * id + 1] : 0.f, g2 = act ? gb[3 * id + 2] : 0.f;
+        float Nu[PM + 1], Nv[QM + 1], su[PM * (PM + 1) / 2], sv[QM * (QM + 1) / 2];
+        span_basis_rt<PM>(tu, p, u, Nu, su);
+        span_basis_rt<QM>(tv, q, v, Nv, sv);
+        // R_r = sum_h Nv_h Pw_rh, Q_h = sum_r Nu_r Pw_rh
+        float4 R[PM + 1], Q[QM + 1], A = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int h = 0; h <= QM; ++h) Q[h] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int r = 0; r <= PM; ++r) {
+            R[r] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (r > p) continue;
+#pragma unroll
+            for (int h = 0; h <= QM; ++h) {
+                if (h > q) continue;
+                const float4 c = L.patch[r * (q + 1) + h];
+                R[r] = fma4(Nv[h], c, R[r]);
+                Q[h] = fma4(Nu[r], c, Q[h]);
+            }
+            A = fma4(Nu[r], R[r], A);
+        }
+        const float iw = recip(A.w);
+        const float h0 = iw * g0, h1 = iw * g1, h2 = iw * g2;
+        const float sg = iw * __builtin_fmaf(A.z, h2, __builtin_fmaf(A.y, h1, A.x * h0));  // (S - c).g / W
+        if (want_pw) {
+            wave_lds_sync();
+#pragma unroll
+            for (int r = 0; r <= PM; ++r)
+                if (r <= p) L.nu[r][lane] = Nu[r];
+#pragma unroll
+            for (int h = 0; h <= QM; ++h)
+                if (h <= q) {
+                    L.tv[4 * h][lane] = Nv[h] * h0;
+                    L.tv[4 * h + 1][lane] = Nv[h] * h1;
+                    L.tv[4 * h + 2][lane] = Nv[h] * h2;
+                    L.tv[4 * h + 3][lane] = -(Nv[h] * sg);
+                }
+            wave_lds_sync();
+        }
+        if (want_ku) {
+            float e[PM + 1], gk[2 * PM];
+#pragma unroll
+            for (int r = 0; r <= PM; ++r)
+                e[r] = __builtin_fmaf(R[r].x, h0, __builtin_fmaf(R[r].y, h1, __builtin_fmaf(R[r].z, h2, -R[r].w * sg)));
+            span_adjoint_rt<PM>(tu, p, u, su, e, gk);
+#pragma unroll
+            for (int i = 0; i < 2 * PM; ++i) sku[i] += (double)gk[i];
+        }
+        if (want_kv) {
+            float f[QM + 1], gk[2 * QM];
+#pragma unroll
+            for (int h = 0; h <= QM; ++h)
+                f[h] = __builtin_fmaf(Q[h].x, h0, __builtin_fmaf(Q[h].y, h1, __builtin_fmaf(Q[h].z, h2, -Q[h].w * sg)));
+            span_adjoint_rt<QM>(tv, q, v, sv, f, gk);
+#pragma unroll
+            for (int i = 0; i < 2 * QM; ++i) skv[i] += (double)gk[i];
+        }
+        if (want_pw) {
+            // pairs past the item's end hold h = 0
+            const int n4 = (min(kWave, s1 - k) + 3) >> 2;
+#pragma unroll 2
+            for (int j = 0; j < n4; ++j) {
+#pragma unroll
+                for (int m = 0; m < kOwn; ++m) {
+                    const float4 x4 = *reinterpret_cast<const float4*>(&L.nu[row_u[m]][4 * j]);
+                    const float4 y4 = *reinterpret_cast<const float4*>(&L.tv[row_v[m]][4 * j]);
+                    acc[m] = __builtin_fma((double)x4.x, (double)y4.x, acc[m]);
+                    acc[m] = __builtin_fma((double)x4.y, (double)y4.y, acc[m]);
+                    acc[m] = __builtin_fma((double)x4.z, (double)y4.z, acc[m]);
+                    acc[m] = __builtin_fma((double)x4.w, (double)y4.w, acc[m]);
+                }
+            }
+        }
+    }
+
+    double* out = t.slots + ((size_t)g * s.items + item) * s.slot;
+    if (want_pw) {
+#pragma unroll
+        for (int m = 0; m < kOwn; ++m) {
+            // M_x, M_y, M_z, M_w of one control point sit in four neighbouring lanes
+            const int l0 = lane & ~3, o = lane + m * kWave;
+            const double mx = __shfl(acc[m], l0), my = __shfl(acc[m], l0 + 1), mz = __shfl(acc[m], l0 + 2);
+            const int src = min(o >> 2, npatch - 1);
+            const float px = __shfl(pc.x, src), py = __shfl(pc.y, src), pz = __shfl(pc.z, src), w = __shfl(pc.w, src);
+            const double dw = (double)px * mx + (double)py * my + (double)pz * mz + acc[m];
+            if (o < 4 * npatch) out[o] = (o & 3) == 3 ? dw : (double)w * acc[m];
+        }
+    }
+    double* buf = reinterpret_cast<double*>(&L.nu[0][0]);
+    if (want_ku) {
+        const double x = wave_sums<2 * PM>(buf, sku, 2 * p);
+        if ((lane & 3) == 0 && (lane >> 2) < 2 * p) out[4 * npatch + (lane >> 2)] = x;
+    }
+    if (want_kv) {
+        const double x = wave_sums<2 * QM>(buf, skv, 2 * q);
+        if ((lane & 3) == 0 && (lane >> 2) < 2 * q) out[4 * npatch + 2 * p + (lane >> 2)] = x;
+    }
+}
+
+// --------------------------------------------------------------------------
+// sums over items
+// --------------------------------------------------------------------------
+// Entry o of every item of cell c, in order.
+__device__ __forceinline__ double cell_sum(const int* __restrict__ is, const double* __restrict__ slots, int slot,
+                                           int c, int o) {
+    double x = 0.0;
+    for (int i = is[c]; i < is[c + 1]; ++i) x += slots[(size_t)i * slot + o];
+    return x;
+}
+
+// Grid (blocks, surfaces).  The first cblk workgroups: one thread per value
+// of a control point; the others: one wave per knot, its lanes over the cells.
+__global__ void __launch_bounds__(kWG) k_uv_sum(UvArgs a, UvSort s, SortPtrs t, int b0, int cblk, unsigned mask,
+                                               float* __restrict__ gc, float* __restrict__ gw,
+                                               float* __restrict__ gku, float* __restrict__ gkv) {
+    const int g = blockIdx.y, b = b0 + g, p = a.p, q = a.q;
+    const int ncu = a.nu_c - p, ncv = s.ncv;
+    const int* is = t.item_start + (size_t)g * (s.cells + 1);
+    const double* slots = t.slots + (size_t)g * s.items * s.slot;
+    if ((int)blockIdx.x < cblk) {
+        const int e = blockIdx.x * kWG + threadIdx.x, ij = e >> 2, c = e & 3;
+        const int ncp = a.nu_c * a.nv_c;
+        if (ij >= ncp || !(mask & (c == 3 ? NURBS_GRAD_W : NURBS_GRAD_CTRL))) return;
+        const int i = ij / a.nv_c, j = ij - i * a.nv_c;
+        double x = 0.0;
+        for (int cu = max(0, i - p); cu <= min(i, ncu - 1); ++cu)
+            for (int cv = max(0, j - q); cv <= min(j, ncv - 1); ++cv)
+                x += cell_sum(is, slots, s.slot, cu * ncv + cv, 4 * ((i - cu) * (q + 1) + j - cv) + c);
+        if (c < 3) gc[3 * ((size_t)b * ncp + ij) + c] = (float)x;
+        else gw[(size_t)b * ncp + ij] = (float)x;
+        return;
+    }
+    const int nU = a.nu_c + p + 1, nV = a.nv_c + q + 1, lane = lane_id();
+    int e = ((int)blockIdx.x - cblk) * kWavesPerWG + (int)threadIdx.x / kWave;
+    if (e >= nU + nV) return;
+    const bool in_v = e >= nU;
+    if (!(mask & (in_v ? NURBS_GRAD_KV : NURBS_GRAD_KU))) return;
+    if (in_v) e -= nU;
+    // knot e is entry e - 1 - c of the window of span cell c of its direction
+    const int d = in_v ? q : p, nc = in_v ? ncv : ncu, other = in_v ? ncu : ncv;
+    const int lo = max(0, e - 2 * d), hi = min(nc - 1, e - 1);
+    const int base = 4 * (p + 1) * (q + 1) + (in_v ? 2 * p : 0);
+    double x = 0.0;
+    const int span = hi - lo + 1;
+    for (int m = lane; m < span * other; m += kWave) {
+        const int c = lo + m / other, o = m % other;
+        x += cell_sum(is, slots, s.slot, in_v ? o * ncv + c : c * ncv + o, base + e - 1 - c);
+    }
+#pragma unroll
+    for (int m = 1; m < kWave; m <<= 1) x += __shfl_xor(x, m);
+    if (lane == 0) (in_v ? gkv + (size_t)b * nV : gku + (size_t)b * nU)[e] = (float)x;
+}
+
+template <int PM, int QM>
+void launch_cell(dim3 grid, hipStream_t st, const UvArgs& a, const UvSort& s, const SortPtrs& t, int b0,
+                 const float* gpts, unsigned mask) {
+    hipLaunchKernelGGL((k_uv_cell<PM, QM>), grid, dim3(kWG), 0, st, a, s, t, b0, gpts, mask);
+}
+
+}  // namespace
+
+bool uv_sort_plan(int B, int p, int q, int nu_c, int nv_c, int npts, size_t head, UvSort* out) {
+    UvSort s{};
+    s.ncv = nv_c - q;
+    const long long cells = (long long)(nu_c - p) * s.ncv;
+    // Where the line lies: below one pair to a cell on average an item's sums
+    // (one slot per cell, read back by every control point) cost more than a
+    // few atomics per pair: 64 surfaces of degree (5, 5), 40 x 40 net and 1000
+    // pairs (1225 cells) take 220 us a pass here and 166 us with the atomics;
+    // with 30000 pairs (B = 8, 48 x 48 net) 188 us here and 3.8 ms there.
+    // Above kUvCellsMax cells the counters of a chunk outgrow their LDS.
+    if (npts < 1 || cells > kUvCellsMax || npts < cells) return false;
+    s.cells = (int)cells;
+    // nothing that fixes the order of a sum depends on B, so that a surface's
+    // result does not depend on the batch it is in
+    const long long c = ((long long)npts + 127) / 128;
+    s.chunk = (int)std::max<long long>(256, (c + kWave - 1) / kWave * kWave);
+    s.nchunk = (npts + s.chunk - 1) / s.chunk;
+    s.seg = npts >= 32768 ? 512 : 128;
+    s.items = (int)(std::min<long long>(cells, npts) + npts / s.seg);
+    s.slot = 4 * (p + 1) * (q + 1) + 2 * p + 2 * q;
+    auto al = [](size_t x) { return (x + 255) & ~size_t(255); };
+    // at most 1 GiB of tables and slots at a time
+    size_t one = al(4 * (size_t)s.nchunk * s.cells) + 2 * al(4 * (size_t)(s.cells + 1)) + al(4 * (size_t)s.items) +
+                 al(6 * (size_t)npts) + al(8 * (size_t)s.items * s.slot);
+    s.group = (int)std::max<long long>(1, std::min<long long>(B, (long long)((size_t(1) << 30) / one)));
+    const size_t G = (size_t)s.group;
+    s.hist = head;
+    s.cell_start = s.hist + al(4 * G * s.nchunk * s.cells);
+    s.item_start = s.cell_start + al(4 * G * (s.cells + 1));
+    s.item_cell = s.item_start + al(4 * G * (s.cells + 1));
+    s.order = s.item_cell + al(4 * G * s.items);
+    s.cell_of = s.order + al(4 * G * npts);
+    s.slots = s.cell_of + al(2 * G * npts);
+    s.total = s.slots + al(8 * G * s.items * s.slot);
+    *out = s;
+    return true;
+}
+
+hipError_t launch_uv_bwd_sorted(const UvArgs& a, const UvSort& s, char* ws, hipStream_t st, const float* gpts,
+                                unsigned mask, float* gc, float* gw, float* gku, float* gkv) {
+    SortPtrs t;
+    t.hist = reinterpret_cast<unsigned*>(ws + s.hist);
+    t.cell_start = reinterpret_cast<int*>(ws + s.cell_start);
+    t.item_start = reinterpret_cast<int*>(ws + s.item_start);
+    t.item_cell = reinterpret_cast<int*>(ws + s.item_cell);
+    t.order = reinterpret_cast<unsigned*>(ws + s.order);
+    t.cell = reinterpret_cast<unsigned short*>(ws + s.cell_of);
+    t.slots = reinterpret_cast<double*>(ws + s.slots);
+    int bits = 0;
+    while ((1 << bits) < s.cells) ++bits;
+    const size_t lds = sizeof(unsigned) * (size_t)s.cells;
+    const int cblk = (4 * a.nu_c * a.nv_c + kWG - 1) / kWG;
+    const int kblk = (a.nu_c + a.p + 1 + a.nv_c + a.q + 1 + kWavesPerWG - 1) / kWavesPerWG;
+    for (int b0 = 0; b0 < a.B; b0 += s.group) {
+        const unsigned nb = (unsigned)std::min(s.group, a.B - b0);
+        hipLaunchKernelGGL(k_uv_hist, dim3((unsigned)s.nchunk, nb), dim3(kWG), lds, st, a, s, t, b0);
+        hipLaunchKernelGGL(k_uv_scan, dim3(nb), dim3(kScanWG), 0, st, s, t);
+        hipLaunchKernelGGL(k_uv_order, dim3((unsigned)s.nchunk, nb), dim3(kWave), lds, st, a, s, t, bits);
+        const dim3 gi((unsigned)((s.items + kWavesPerWG - 1) / kWavesPerWG), nb);
+        const int m = std::max(a.p, a.q);
+        if (m <= 3) launch_cell<3, 3>(gi, st, a, s, t, b0, gpts, mask);
+        else if (m <= 5) launch_cell<5, 5>(gi, st, a, s, t, b0, gpts, mask);
+        else launch_cell<7, 7>(gi, st, a, s, t, b0, gpts, mask);
+        hipLaunchKernelGGL(k_uv_sum, dim3((unsigned)(cblk + kblk), nb), dim3(kWG), 0, st, a, s, t, b0, cblk, mask, gc,
+                           gw, gku, gkv);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+}  // namespace nd

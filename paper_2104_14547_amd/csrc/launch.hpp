@@ -136,6 +136,23 @@ struct UvArgs {
     int fchunk;   // pairs per forward workgroup
     int* err;     // device error word (NURBS_VALIDATE) or NULL
 };
+
+// Scattered backward over pairs ordered by cell (k_uv_cells.hip): the sizes
+// for one surface shape and the byte offsets in the workspace of a group of
+// `group` surfaces (the batch is taken a group at a time).
+constexpr int kUvCellsMax = 4096;  // cells whose counters a workgroup keeps in LDS
+struct UvSort {
+    int cells, ncv;    // (nu_c - p)(nv_c - q) cells, ncv = nv_c - q to a row
+    int chunk, nchunk; // pairs per ordering chunk, chunks per surface
+    int seg;           // pairs per item (a cell's pairs are cut into items)
+    int items;         // most items a surface can have
+    int slot;          // doubles per item: 4(p+1)(q+1) + 2p + 2q
+    int group;         // surfaces per pass over the workspace
+    size_t hist, cell_start, item_start, item_cell, order, cell_of, slots, total;
+};
+bool uv_sort_plan(int B, int p, int q, int nu_c, int nv_c, int npts, size_t head, UvSort* out);
+hipError_t launch_uv_bwd_sorted(const UvArgs& a, const UvSort& s, char* ws, hipStream_t st, const float* gpts,
+                                unsigned mask, float* gc, float* gw, float* gku, float* gkv);
 constexpr int kUvLdsAccMax = 7424;                 // accumulators a workgroup keeps in LDS (58 KiB)
 constexpr size_t kUvLdsDynMax = 60 * 1024 - 2048;  // dynamic LDS per workgroup (static: the knots)
 hipError_t launch_uv_fwd(const UvArgs& a, hipStream_t st, float* pts, float* du, float* dv);
