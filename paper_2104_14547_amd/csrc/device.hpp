@@ -286,7 +286,7 @@ __device__ __forceinline__ void span_basis(const float* K, const float* inv, flo
     }
 }
 
-// gK[t] = d/dK[t] of sum_r e[r] N_{k-D+r}(x); the outermost knots U_{k-D} and
+// gK[t] += d/dK[t] of sum_r e[r] N_{k-D+r}(x); the outermost knots U_{k-D} and
 // U_{k+D+1} of the functions' supports do not enter on span k.
 template <int D>
 __device__ __forceinline__ void span_adjoint(const float* K, const float* inv, float x, const float* s,
@@ -294,8 +294,6 @@ __device__ __forceinline__ void span_adjoint(const float* K, const float* inv, f
     float A[D + 1];
 #pragma unroll
     for (int r = 0; r <= D; ++r) A[r] = e[r];
-#pragma unroll
-    for (int t = 0; t < 2 * D; ++t) gK[t] = 0.0f;
 #pragma unroll
     for (int d = D; d >= 1; --d)
 #pragma unroll

@@ -15,20 +15,21 @@
 // (Sec. 3.2.1).  dL/dw is taken directly from P_i - C (not as P . dL/dPw +
 // dL/dPw_w), so no difference of two large sums is formed.
 //
-// Work decomposition.  A workgroup (4 waves) owns one chunk of up to
-// kCurveChunk consecutive samples of one curve and stages that curve's knots
-// and control polygon in LDS.  A wave handles 64 consecutive samples at a
-// time, one per lane.  Backward contributions are reduced without atomics:
-// when the 64 spans of a wave are non-decreasing (sorted parameters, the
-// usual case), equal spans form runs of lanes and a DPP segmented scan (the
-// surface backward's, one v_fmac_f32_dpp per value and step) sums each run,
-// whose last lane adds the sums into the wave's LDS accumulators; an
-// unsorted wave adds its lanes one after the other.  At the end of the
-// chunk the four waves' accumulators are added in wave order.  A curve with
-// one chunk writes its gradients directly; longer curves write one partial
-// per chunk to the workspace and a finalize kernel adds the partials in
-// chunk order.  Every sum has a fixed order, so results are bitwise
-// reproducible.
+// Work decomposition.  A workgroup (4 waves, 1 to 4 in the backward) owns one chunk
+// of up to kCurveChunk consecutive samples of one curve and stages that
+// curve's knots and control polygon in LDS.  Forward: one sample per lane.  Backward: the
+// chunk's samples are put in span order (sorted parameters, the usual case,
+// are in it already; others go through a stable counting sort in LDS) and the
+// samples of a span are cut into items, one item per lane at a time.  Lanes of one span form runs; a DPP segmented scan (the surface
+// backward's, one v_fmac_f32_dpp per value and step) sums each run, whose last
+// lane adds the sums into the wave's LDS accumulators, without atomics.  At
+// the end of the chunk the waves' accumulators are added in wave order.
+// A curve with one chunk writes its gradients directly; longer curves write
+// one partial per chunk to the workspace and a finalize kernel adds the
+// partials in chunk order.  Every sum has a fixed order, so results are
+// bitwise reproducible.
+#include <algorithm>
+
 #include "kernels.hpp"
 #include "launch.hpp"
 #include "../../include/nurbsdiff.h"
@@ -48,12 +49,12 @@ __device__ void curve_validate(const CurveArgs& a, int p, int c, int chunk, int 
     const int nU = a.nc + p + 1;
     bool bad_k = false, bad_w = false, bad_d = false;
     if (chunk == 0) {
-        for (int i = t; i + 1 < nU; i += kWG) bad_k |= !(U[i] <= U[i + 1]);
+        for (int i = t; i + 1 < nU; i += blockDim.x) bad_k |= !(U[i] <= U[i + 1]);
         if (t == 0) bad_k |= !(U[p] < U[p + 1]) || !(U[a.nc - 1] < U[a.nc]);
-        for (int i = t; i < a.nc; i += kWG) bad_w |= !(w[i] > 0.f);
+        for (int i = t; i < a.nc; i += blockDim.x) bad_w |= !(w[i] > 0.f);
     }
     const float lo = U[p], hi = U[a.nc];
-    for (int s = s0 + t; s < s1; s += kWG) bad_d |= !(us[s] >= lo && us[s] <= hi);
+    for (int s = s0 + t; s < s1; s += blockDim.x) bad_d |= !(us[s] >= lo && us[s] <= hi);
     if (bad_k) curve_post_error(a.err, NURBS_EKNOTS);
     if (bad_w) curve_post_error(a.err, NURBS_EWEIGHTS);
     if (bad_d) curve_post_error(a.err, NURBS_EDOMAIN);
@@ -80,8 +81,8 @@ __device__ __forceinline__ void stage_curve(const CurveArgs& a, int p, int c, fl
     const float* kn = a.knots + (size_t)c * nU;
     const float* cp = a.ctrl + (size_t)c * a.nc * DIM;
     const float* w = a.w + (size_t)c * a.nc;
-    for (int i = threadIdx.x; i < nU; i += kWG) U[i] = kn[i];
-    for (int i = threadIdx.x; i < a.nc; i += kWG)
+    for (int i = threadIdx.x; i < nU; i += blockDim.x) U[i] = kn[i];
+    for (int i = threadIdx.x; i < a.nc; i += blockDim.x)
         Pw[i] = make_float4(cp[i * DIM], cp[i * DIM + 1], DIM == 3 ? cp[i * DIM + 2] : 0.f, w[i]);
 }
 
@@ -130,148 +131,339 @@ __global__ void __launch_bounds__(kWG) k_curve_fwd(CurveArgs a, float* __restric
 // backward
 // --------------------------------------------------------------------------
 
-// per-wave accumulators: control point i -> (dL/dP_i xyz, dL/dw_i); knot t -> dL/dU_t
-struct CurveAcc {
-    float4 cp[kWG];
-    float kn[kWG];
+// Waves of a backward workgroup, by the samples of its chunk: enough that a
+// lane's item holds several samples, few enough that a pass over the items
+// fills every wave (four waves for a thousand samples left one of them idle:
+// 227 us against 155 us), and with one wave the workgroup's barriers cost
+// nothing.
+constexpr int curve_waves(int chunk) { return chunk <= 384 ? 1 : chunk <= 1024 ? 2 : 4; }
+
+// The workgroup's LDS (dynamic, sized by the curve's control points).
+struct CurveLds {
+    float4 *pw;       // [nc] control points (xyz, w)
+    float4 *acc;      // [waves][nc]: (dL/dP xyz, dL/dw)
+    float *U, *acck;  // [nU], [waves][nU]
+    float *us;        // [chunk] parameters, clamped into the domain
+    int *first;       // [spans + 1]: first sample (in span order) of each span
+    int *item;        // [spans + 1]: first item of each span
+    int *hist;        // [waves][spans]: unsorted parameters only
+    int *wsum;        // [waves]
+    unsigned short *perm;  // [chunk]: unsorted parameters only
+};
+__host__ __device__ inline size_t curve_lds_bytes(int waves, int nc, int p, int chunk) {
+    const size_t nU = nc + p + 1, ns = nc - p;
+    return 16 * (size_t)nc * (1 + waves) + 4 * nU * (1 + waves) + 4 * (2 * (ns + 1) + waves * (ns + 1)) +
+           6 * (size_t)chunk;
+}
+template <int W>
+__device__ __forceinline__ CurveLds curve_lds(char* base, int nc, int p, int chunk) {
+    const int nU = nc + p + 1, ns = nc - p;
+    CurveLds l;
+    l.pw = reinterpret_cast<float4*>(base);
+    l.acc = l.pw + nc;
+    l.U = reinterpret_cast<float*>(l.acc + W * nc);
+    l.acck = l.U + nU;
+    l.us = l.acck + W * nU;
+    l.first = reinterpret_cast<int*>(l.us + chunk);
+    l.item = l.first + ns + 1;
+    l.hist = l.item + ns + 1;
+    l.wsum = l.hist + W * ns;
+    l.perm = reinterpret_cast<unsigned short*>(l.wsum + W);
+    return l;
+}
+
+// Exclusive prefix over the spans' counts n(0), n(1), ..., n(spans - 1) into
+// out[0 .. spans], out[spans] the total.
+template <int W, class N>
+__device__ __forceinline__ int span_prefix(const CurveLds& l, int spans, int* out, const N& n) {
+    const int t = threadIdx.x;
+    int all = 0;
+    for (int c0 = 0; c0 < spans; c0 += W * kWave) {
+        const int v = c0 + t < spans ? n(c0 + t) : 0;
+        int x = v;
+#pragma unroll
+        for (int d = 1; d < kWave; d <<= 1) {
+            const int y = __shfl_up(x, d);
+            if (lane_id() >= d) x += y;
+        }
+        int sum = 0;
+        if constexpr (W == 1) {
+            sum = bcast_lane(x, kWave - 1);
+        } else {
+            __syncthreads();
+            if (lane_id() == kWave - 1) l.wsum[t / kWave] = x;
+            __syncthreads();
+            int before = 0;
+#pragma unroll
+            for (int w = 0; w < W; ++w) {
+                if (w < t / kWave) before += l.wsum[w];
+                sum += l.wsum[w];
+            }
+            x += before;
+        }
+        if (c0 + t < spans) out[c0 + t] = all + x - v;
+        all += sum;
+    }
+    if (t == 0) out[spans] = all;
+    __syncthreads();
+    return all;
+}
+
+// Put the chunk's n samples (l.us) in span order: l.first, and l.perm when the
+// parameters are not sorted (returns whether they are).  The order within a
+// span is the input's.
+template <int W>
+__device__ __forceinline__ bool curve_order(const CurveLds& l, int p, int nc, int n) {
+    constexpr int kT = W * kWave;
+    const int t = threadIdx.x, spans = nc - p, wv = t / kWave, lane = lane_id();
+    bool bad = false;
+    for (int s = t + 1; s < n; s += kT) bad |= !(l.us[s - 1] <= l.us[s]);
+    // knots out of order (only flagged, under NURBS_VALIDATE) go by find_span,
+    // which stays in range whatever they are
+    for (int c = t; c < spans; c += kT) bad |= !(l.U[p + c] <= l.U[p + c + 1]);
+    if (t == 0) bad |= !(l.U[nc - 1] < l.U[nc]);
+    if (!__syncthreads_or(bad)) {
+        // sorted: a span starts at the first sample not below its knot, one
+        // search per knot instead of one per sample; an empty span starts
+        // where the next one does
+        for (int c = t; c <= spans; c += kT) {
+            const float x = l.U[p + c];
+            int lo = c == spans ? n : 0, hi = n;
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (l.us[mid] < x) lo = mid + 1; else hi = mid;
+            }
+            l.first[c] = lo;
+        }
+        __syncthreads();
+        return true;
+    }
+    // stable counting sort: each wave takes its part of the samples
+    auto span_of = [&](int s) { return find_span(l.U, p, nc - 1, l.us[s]) - p; };
+    for (int i = t; i < W * spans; i += kT) l.hist[i] = 0;
+    __syncthreads();
+    const int per = (n + kT - 1) / kT * kWave;
+    const int q0 = min(n, wv * per), q1 = min(n, q0 + per);
+    int* h = l.hist + wv * spans;
+    for (int s = q0 + lane; s < q1; s += kWave) atomicAdd(h + span_of(s), 1);
+    __syncthreads();
+    span_prefix<W>(l, spans, l.first, [&](int c) {
+        int x = 0;
+        for (int w = 0; w < W; ++w) x += l.hist[w * spans + c];
+        return x;
+    });
+    for (int c = t; c < spans; c += kT) {
+        int at = l.first[c];
+        for (int w = 0; w < W; ++w) {
+            const int x = l.hist[w * spans + c];
+            l.hist[w * spans + c] = at;
+            at += x;
+        }
+    }
+    __syncthreads();
+    int bits = 0;
+    while ((1 << bits) < spans) ++bits;
+    for (int s = q0; s < q1; s += kWave) {
+        const bool act = s + lane < q1;
+        const int k = act ? span_of(s + lane) : 0;
+        // lanes of the same span
+        unsigned long long m = __ballot(act);
+        for (int i = 0; i < bits; ++i) {
+            const bool bit = (k >> i) & 1;
+            const unsigned long long v = __ballot(bit);
+            m &= bit ? v : ~v;
+        }
+        const int rank = __popcll(m & ((1ull << lane) - 1ull));
+        const int base = h[k];
+        wave_lds_sync();
+        if (act && rank == 0) h[k] = base + __popcll(m);
+        wave_lds_sync();
+        if (act) l.perm[base + rank] = (unsigned short)(s + lane);
+    }
+    __syncthreads();
+    return false;
+}
+
+// Cut the spans into items of at most the returned number of samples; l.item.
+// A lane's samples share their span, so the span's knots, reciprocals and
+// control points are read once for all of them and the sums over them stay in
+// registers; the scan over the wave and the LDS adds come once per 64 items.
+// The length is the least that fills the waves once (a multiple of that for
+// curves of many spans): an item more than the lanes would cost a whole pass.
+template <int W>
+__device__ __forceinline__ int curve_items(const CurveLds& l, int spans, int n, int* nitems) {
+    constexpr int kT = W * kWave;
+    int used = 0;
+    for (int c0 = 0; c0 < spans; c0 += kT) {
+        const int c = c0 + (int)threadIdx.x;
+        used += __syncthreads_count(c < spans && l.first[c + 1] > l.first[c]);
+    }
+    const int room = kT * ((used + kWave - 1) / kWave);
+    int len = (2 * n + 2 * room - used - 1) / (2 * room - used);  // half an item lost per span
+    auto count = [&](int c) { return (l.first[c + 1] - l.first[c] + len - 1) / len; };
+    *nitems = span_prefix<W>(l, spans, l.item, count);
+    if (*nitems > room) {
+        len = (n + room - used - 1) / (room - used);  // a whole one: fits
+        *nitems = span_prefix<W>(l, spans, l.item, count);
+    }
+    return len;
+}
+
+// One sample's parameter (from LDS) and dL/dC.
+template <int DIM>
+struct CurveSample {
+    float u, g[3];
+    __device__ __forceinline__ void load(const float* us, const float* gpts, int s) {
+        u = us[s];
+        const float* p = gpts + (size_t)s * DIM;
+        if constexpr (DIM == 3) {
+            const float3u v = *reinterpret_cast<const float3u*>(p);
+            g[0] = v.x;
+            g[1] = v.y;
+            g[2] = v.z;
+        } else {
+            g[0] = p[0];
+            g[1] = p[1];
+            g[2] = 0.f;
+        }
+    }
 };
 
-template <int P, int DIM>
-__global__ void __launch_bounds__(kWG) k_curve_bwd(CurveArgs a, const float* __restrict__ gpts,
-                                                   float* __restrict__ gctrl, float* __restrict__ gw,
-                                                   float* __restrict__ gk, float* __restrict__ part,
-                                                   unsigned mask) {
-    __shared__ float U[kWG];
-    __shared__ float4 Pw[kWG];
-    __shared__ CurveAcc acc[kWavesPerWG];
+// What bounds it: VALU issue of the per-sample work (basis, curve point,
+// adjoint): about 150 instructions a step, 7.0e7 wave instructions (113 us of
+// issue) for 16384 cubic space curves of 32 control points x 1024 samples,
+// 150 us in all.  One sample per lane with a wave-wide scan and LDS adds for
+// every 64 samples, a search per sample and the adjoint's reciprocals taken
+// twice took 270-300 us.  Items of a lane's own consecutive samples, so that
+// its reads lie hundreds of bytes from its neighbours': 155 us (at degree 1,
+// 64 control points, 4096 x 4096 samples 285 us a pass against 160); dL/dC
+// staged in LDS: 189 us (fewer workgroups resident).  Parameters in random
+// order (4096 quartic curves x 1000 samples): 847 -> 112 us a pass.
+template <int P, int DIM, int W>
+__global__ void __launch_bounds__(W* kWave) k_curve_bwd(CurveArgs a, const float* __restrict__ gpts,
+                                                        float* __restrict__ gctrl, float* __restrict__ gw,
+                                                        float* __restrict__ gk, float* __restrict__ part,
+                                                        unsigned mask) {
+    extern __shared__ float4 curve_dyn[];
+    constexpr int kT = W * kWave;
     const CurveBlock b = curve_block(a);
-    const int nU = a.nc + P + 1;
-    stage_curve<DIM>(a, P, b.c, U, Pw);
-    for (int wv = 0; wv < kWavesPerWG; ++wv)
-        for (int i = threadIdx.x; i < kWG; i += kWG) {
-            acc[wv].cp[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-            acc[wv].kn[i] = 0.f;
-        }
-    __syncthreads();
+    const int nU = a.nc + P + 1, spans = a.nc - P, n = b.s1 - b.s0;
+    const CurveLds l = curve_lds<W>(reinterpret_cast<char*>(curve_dyn), a.nc, P, min(a.ns, kCurveChunk));
     const float* us = a.us + (a.u_shared ? 0 : (size_t)b.c * a.ns);
-    if (a.err) curve_validate(a, P, b.c, b.chunk, b.s0, b.s1, U, a.w + (size_t)b.c * a.nc, us);
+    stage_curve<DIM>(a, P, b.c, l.U, l.pw);
+    for (int i = threadIdx.x; i < n; i += kT) l.us[i] = us[b.s0 + i];
+    const float* g0 = gpts + ((size_t)b.c * a.ns + b.s0) * DIM;
+    for (int i = threadIdx.x; i < W * a.nc; i += kT) l.acc[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int i = threadIdx.x; i < W * nU; i += kT) l.acck[i] = 0.f;
+    __syncthreads();
+    if (a.err) curve_validate(a, P, b.c, b.chunk, b.s0, b.s1, l.U, a.w + (size_t)b.c * a.nc, us);
+    for (int i = threadIdx.x; i < n; i += kT) l.us[i] = clamp_param(l.U, P, a.nc - 1, l.us[i]);
+    __syncthreads();
+    const bool in_order = curve_order<W>(l, P, a.nc, n);
+    int nitems;
+    const int len = curve_items<W>(l, spans, n, &nitems);
     const bool want_k = (mask & NURBS_GRAD_KU) != 0;
     const int wv = threadIdx.x / kWave;
     const int lane = lane_id();
-    CurveAcc& A = acc[wv];
-    const float* g0 = gpts + (size_t)b.c * a.ns * DIM;
-    constexpr int kSentinel = 1 << 20;  // span of lanes past the chunk end
-    for (int base = b.s0 + wv * kWave; base < b.s1; base += kWG) {
-        const int s = base + lane;
-        const bool act = s < b.s1;
-        // per control point r of the sample's span: (dL/dP xyz, dL/dw)
+    float4* acc = l.acc + wv * a.nc;
+    float* acck = l.acck + wv * nU;
+    constexpr int kSentinel = 1 << 20;  // span of lanes past the last item
+    for (int base = wv * kWave; base < nitems; base += kT) {
+        const bool act = base + lane < nitems;
+        const int it = min(base + lane, nitems - 1);
+        // the item's span: the last one that starts at or before it
+        int lo = 0, hi = spans;
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (l.item[mid] <= it) lo = mid; else hi = mid;
+        }
+        // the m items of a span take its samples in turn, so that their lanes
+        // read neighbouring samples at each step
+        const int m = l.item[lo + 1] - l.item[lo], j1 = l.first[lo + 1];
+        int i = l.first[lo] + it - l.item[lo];
+        const int k = lo + P;
+        float K[2 * P], inv[P * (P + 1) / 2];
+#pragma unroll
+        for (int t = 0; t < 2 * P; ++t) K[t] = l.U[k - P + 1 + t];
+        span_inv<P>(K, inv);
+        float4 q[P + 1];
+#pragma unroll
+        for (int r = 0; r <= P; ++r) q[r] = l.pw[k - P + r];
+        // per control point r of the span: (dL/dP xyz, dL/dw); per knot of its window
         float4 c4[P + 1];
-        float gU[2 * P + 2];
-        int k = kSentinel;
+        float gU[2 * P];
 #pragma unroll
         for (int r = 0; r <= P; ++r) c4[r] = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-        for (int t = 0; t < 2 * P + 2; ++t) gU[t] = 0.f;
-        if (act) {
-            const float x = clamp_param(U, P, a.nc - 1, us[s]);
-            k = find_span(U, P, a.nc - 1, x);
-            float N[P + 1];
-            basis_f32<P>(U, k, x, N);
-            float Wsum = 0.f, C[3] = {0.f, 0.f, 0.f};
+        for (int t = 0; t < 2 * P; ++t) gU[t] = 0.f;
+        // one sample ahead: the loads of the next overlap the current one's work
+        CurveSample<DIM> nx;
+        nx.load(l.us, g0, in_order ? i : (int)l.perm[i]);
+#pragma unroll 1
+        for (int j = 0; j < len; ++j, i += m) {
+            const CurveSample<DIM> x = nx;
+            const int ni = min(i + m, j1 - 1);
+            nx.load(l.us, g0, in_order ? ni : (int)l.perm[ni]);
+            const float u = x.u;
+            float N[P + 1], st[P * (P + 1) / 2];
+            span_basis<P>(K, inv, u, N, st);
+            float Wsum = 0.f, C[3] = {0.f, 0.f, 0.f}, Nw[P + 1];
 #pragma unroll
             for (int r = 0; r <= P; ++r) {
-                const float4 q = Pw[k - P + r];
-                const float c = N[r] * q.w;
-                Wsum += c;
-                C[0] = __builtin_fmaf(c, q.x, C[0]);
-                C[1] = __builtin_fmaf(c, q.y, C[1]);
-                if constexpr (DIM == 3) C[2] = __builtin_fmaf(c, q.z, C[2]);
+                Nw[r] = N[r] * q[r].w;
+                Wsum += Nw[r];
+                C[0] = __builtin_fmaf(Nw[r], q[r].x, C[0]);
+                C[1] = __builtin_fmaf(Nw[r], q[r].y, C[1]);
+                if constexpr (DIM == 3) C[2] = __builtin_fmaf(Nw[r], q[r].z, C[2]);
             }
-            const float inv = recip(Wsum);
+            const float ic = recip(Wsum);
+            const float iw = i < j1 && act ? ic : 0.f;  // 0: no sample, no contribution
+            const float h[3] = {x.g[0] * iw, x.g[1] * iw, x.g[2] * iw};
 #pragma unroll
-            for (int x2 = 0; x2 < DIM; ++x2) C[x2] *= inv;
-            const float g[3] = {g0[(size_t)s * DIM], g0[(size_t)s * DIM + 1],
-                                DIM == 3 ? g0[(size_t)s * DIM + 2] : 0.f};
+            for (int d = 0; d < DIM; ++d) C[d] *= ic;
             float e[P + 1];
 #pragma unroll
             for (int r = 0; r <= P; ++r) {
-                const float4 q = Pw[k - P + r];
-                float pg = (q.x - C[0]) * g[0];
-                pg = __builtin_fmaf(q.y - C[1], g[1], pg);
-                if constexpr (DIM == 3) pg = __builtin_fmaf(q.z - C[2], g[2], pg);
-                const float nw = N[r] * q.w * inv;
-                c4[r] = make_float4(nw * g[0], nw * g[1], nw * g[2], N[r] * pg * inv);
-                e[r] = q.w * pg * inv;
+                float pg = (q[r].x - C[0]) * h[0];
+                pg = __builtin_fmaf(q[r].y - C[1], h[1], pg);
+                if constexpr (DIM == 3) pg = __builtin_fmaf(q[r].z - C[2], h[2], pg);
+                c4[r].x = __builtin_fmaf(Nw[r], h[0], c4[r].x);
+                c4[r].y = __builtin_fmaf(Nw[r], h[1], c4[r].y);
+                if constexpr (DIM == 3) c4[r].z = __builtin_fmaf(Nw[r], h[2], c4[r].z);
+                c4[r].w = __builtin_fmaf(N[r], pg, c4[r].w);
+                e[r] = q[r].w * pg;
             }
-            if (want_k) basis_knot_adjoint<P>(U, k, x, e, gU);
+            if (want_k) {
+                span_adjoint<P>(K, inv, u, st, e, gU);
+            }
         }
-        // spans non-decreasing across the wave?
-        int kprev = __shfl_up(k, 1);
-        if (lane == 0) kprev = k;
-        const bool sorted = __ballot(k < kprev) == 0ull;
-        if (sorted) {
-            // runs of equal spans: DPP segmented scans, then the last lane of
-            // each run adds the run's sums; for a fixed r the run ends touch
-            // distinct control points
-            const Runs rn = wave_runs(k);
+        // runs of lanes on one span: DPP segmented scans, then the last lane
+        // of each run adds the run's sums; for a fixed r the run ends touch
+        // distinct control points
+        const Runs rn = wave_runs(act ? k : kSentinel);
 #pragma unroll
-            for (int r = 0; r <= P; ++r) seg_scan4(c4[r], rn);
-            if (want_k) {
+        for (int r = 0; r <= P; ++r) seg_scan4(c4[r], rn);
+        if (want_k) {
 #pragma unroll
-                for (int t = 0; t < 2 * P + 2; t += 2) seg_scan2(gU[t], gU[t + 1], rn);
+            for (int t = 0; t < 2 * P; t += 2) seg_scan2(gU[t], gU[t + 1], rn);
+        }
+        const bool wr = rn.head && act;
+#pragma unroll
+        for (int r = 0; r <= P; ++r) {
+            if (wr) {
+                float4 v = acc[k - P + r];
+                v.x += c4[r].x;
+                v.y += c4[r].y;
+                if constexpr (DIM == 3) v.z += c4[r].z;
+                v.w += c4[r].w;
+                acc[k - P + r] = v;
             }
-            const bool wr = rn.head && k != kSentinel;
+            wave_lds_sync();
+        }
+        if (want_k) {
 #pragma unroll
-            for (int r = 0; r <= P; ++r) {
-                if (wr) {
-                    float4 v = A.cp[k - P + r];
-                    v.x += c4[r].x;
-                    v.y += c4[r].y;
-                    if constexpr (DIM == 3) v.z += c4[r].z;
-                    v.w += c4[r].w;
-                    A.cp[k - P + r] = v;
-                }
-                wave_lds_sync();
-            }
-            if (want_k) {
-#pragma unroll
-                for (int t = 0; t < 2 * P + 2; ++t) {
-                    if (wr) A.kn[k - P + t] += gU[t];
-                    wave_lds_sync();
-                }
-            }
-        } else {
-            // unsorted parameters: the lanes' contributions one after the
-            // other, lane r (r <= P) adding the r-th control point of each
-            // sample and lane t (t <= 2P+1) its t-th knot
-            for (int l = 0; l < kWave; ++l) {
-                const int kl = __builtin_amdgcn_readlane(k, l);
-                if (kl == kSentinel) break;
-                float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-                for (int r = 0; r <= P; ++r) {
-                    const float px = bcast_lane(c4[r].x, l), py = bcast_lane(c4[r].y, l);
-                    const float pz = DIM == 3 ? bcast_lane(c4[r].z, l) : 0.f;
-                    const float pw = bcast_lane(c4[r].w, l);
-                    if (lane == r) v = make_float4(px, py, pz, pw);
-                }
-                if (lane <= P) {
-                    float4 o = A.cp[kl - P + lane];
-                    o.x += v.x;
-                    o.y += v.y;
-                    o.z += v.z;
-                    o.w += v.w;
-                    A.cp[kl - P + lane] = o;
-                }
-                if (want_k) {
-                    float gv = 0.f;
-#pragma unroll
-                    for (int t = 0; t < 2 * P + 2; ++t) {
-                        const float y = bcast_lane(gU[t], l);
-                        if (lane == t) gv = y;
-                    }
-                    if (lane < 2 * P + 2) A.kn[kl - P + lane] += gv;
-                }
+            for (int t = 0; t < 2 * P; ++t) {
+                if (wr) acck[k - P + 1 + t] += gU[t];
                 wave_lds_sync();
             }
         }
@@ -280,11 +472,11 @@ __global__ void __launch_bounds__(kWG) k_curve_bwd(CurveArgs a, const float* __r
     // the chunk's totals, waves added in order
     const bool direct = a.nchunks == 1;
     float* pc = direct ? nullptr : part + ((size_t)b.c * a.nchunks + b.chunk) * a.part_floats;
-    for (int i = threadIdx.x; i < a.nc; i += kWG) {
-        float4 v = acc[0].cp[i];
+    for (int i = threadIdx.x; i < a.nc; i += kT) {
+        float4 v = l.acc[i];
 #pragma unroll
-        for (int w2 = 1; w2 < kWavesPerWG; ++w2) {
-            const float4 o = acc[w2].cp[i];
+        for (int w2 = 1; w2 < W; ++w2) {
+            const float4 o = l.acc[w2 * a.nc + i];
             v.x += o.x;
             v.y += o.y;
             v.z += o.z;
@@ -303,10 +495,10 @@ __global__ void __launch_bounds__(kWG) k_curve_bwd(CurveArgs a, const float* __r
         }
     }
     if (want_k) {
-        for (int t = threadIdx.x; t < nU; t += kWG) {
-            float v = acc[0].kn[t];
+        for (int t = threadIdx.x; t < nU; t += kT) {
+            float v = l.acck[t];
 #pragma unroll
-            for (int w2 = 1; w2 < kWavesPerWG; ++w2) v += acc[w2].kn[t];
+            for (int w2 = 1; w2 < W; ++w2) v += l.acck[w2 * nU + t];
             if (direct) gk[(size_t)b.c * nU + t] = v;
             else pc[4 * a.nc + t] = v;
         }
@@ -357,11 +549,21 @@ hipError_t curve_fwd_launch(const CurveArgs& a, hipStream_t st, float* pts, floa
     return hipGetLastError();
 }
 
+template <int P, int DIM, int W>
+void curve_bwd_kernel(const CurveArgs& a, hipStream_t st, const float* gpts, float* gctrl, float* gw, float* gk,
+                      float* part, unsigned mask) {
+    const dim3 grid((unsigned)((long long)a.B * a.nchunks));
+    const size_t lds = curve_lds_bytes(W, a.nc, P, std::min(a.ns, kCurveChunk));
+    hipLaunchKernelGGL((k_curve_bwd<P, DIM, W>), grid, dim3(W * kWave), lds, st, a, gpts, gctrl, gw, gk, part, mask);
+}
+
 template <int P, int DIM>
 hipError_t curve_bwd_launch(const CurveArgs& a, hipStream_t st, const float* gpts, float* gctrl, float* gw,
                             float* gk, float* part, unsigned mask) {
-    const dim3 grid((unsigned)((long long)a.B * a.nchunks));
-    hipLaunchKernelGGL((k_curve_bwd<P, DIM>), grid, dim3(kWG), 0, st, a, gpts, gctrl, gw, gk, part, mask);
+    const int w = curve_waves(std::min(a.ns, kCurveChunk));
+    if (w == 1) curve_bwd_kernel<P, DIM, 1>(a, st, gpts, gctrl, gw, gk, part, mask);
+    else if (w == 2) curve_bwd_kernel<P, DIM, 2>(a, st, gpts, gctrl, gw, gk, part, mask);
+    else curve_bwd_kernel<P, DIM, 4>(a, st, gpts, gctrl, gw, gk, part, mask);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || a.nchunks == 1) return e;
     const long long items = (long long)a.B * (2 * a.nc + P + 1);
