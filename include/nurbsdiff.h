@@ -129,7 +129,9 @@ int nurbs_ctx_set_flags(nurbs_ctx *ctx, unsigned flags);
 int nurbs_ctx_set_knot_sigma(nurbs_ctx *ctx, float sigma);
 /* Tiling of later calls on this context: the target number of sample points
  * per forward / backward tile (a tile is one wave over <= 64 sample columns
- * and as many rows as reach the target; 0 restores the default, 16384).
+ * and as many rows as reach the target; 0 restores the default: backward
+ * tiles of about 72 sample rows, forward tiles of 8 to 64 rows by the size of the
+ * batch, which no result depends on).
  * Results stay bitwise reproducible for a given tiling; different tilings
  * change the summation order of the backward within the tolerances.  An
  * autotuner picks these per workload. */
@@ -256,9 +258,9 @@ int nurbs_surface_bwd_tab(nurbs_ctx *ctx, int B, int p, int q, int nu_c, int nv_
  * that the library keeps in device memory (one per device it runs on, held
  * until the process ends).  Arguments, outputs and results as
  * nurbs_surface_bwd, bit for bit.
- * Limits and errors: NURBS_EWORKSPACE when the shapes need more than the
- * 64 MiB that nurbs_surface_ws_bytes would report (use nurbs_surface_bwd
- * with a workspace then); NURBS_EUNSUPPORTED under NURBS_VALIDATE (no data
+ * Limits and errors: NURBS_EWORKSPACE when the slots of all surfaces, counted
+ * in tiles of 16384 points (or those of nurbs_ctx_set_tiling), exceed 64 MiB
+ * (use nurbs_surface_bwd with a workspace then); NURBS_EUNSUPPORTED under NURBS_VALIDATE (no data
  * checks here); NURBS_EINVAL when the context's device is not current at
  * the first call on that device.  The call itself allocates nothing (no
  * hipMalloc, hipFree or allocating library routine).
@@ -495,7 +497,7 @@ int nurbs_read_device_error(const void *ws, void *stream, int *code);
  * arena of slot_bytes and pinned host buffer of slot_bytes, so up to n_slots
  * batches are in flight.  A request's result does not depend on the other
  * requests of its batch, bit for bit (the plan's tiles follow each surface's
- * own shape; the tiling is the context default).
+ * own shape, 16384 points to a tile).
  * ---------------------------------------------------------------------- */
 typedef struct nurbs_server nurbs_server;
 

@@ -24,8 +24,8 @@ struct nurbs_ctx {
     unsigned flags = 0;
     int num_cus = 0;
     int occ[2][2] = {{0, 0}, {0, 0}};  // persistent-kernel workgroups per CU: [class d5, d7][fwd, bwd]
-    int fwd_tile_pts = 16384;          // target points per forward / backward tile
-    int bwd_tile_pts = 16384;
+    int fwd_tile_pts = 0;              // target points per forward / backward tile (0: the default)
+    int bwd_tile_pts = 0;
     int schedule = NURBS_SCHED_STATIC;  // of plans created on this context
     std::string err;
 };
@@ -107,6 +107,26 @@ int check_shape(nurbs_ctx* c, int p, int q, int nu_c, int nv_c, int nu_s, int nv
 // the same tiling -- and bitwise the same result -- alone, in a uniform
 // batch or in any ragged mix.  A tile is one wave64 over min(64, nv_s)
 // columns; the row count aims at a fixed number of points per tile.
+// Rows of a backward tile when the caller set none (nurbs_ctx_set_tiling), in
+// uniform batches and plans alike: the surface's rows in equal parts of about
+// kDefaultRows.  The rows fix the order of the sums, and a surface's gradients
+// depend neither on its batch nor on the kind of call, so the rule looks at
+// its rows alone.  A tile's rows run one after the other (about 0.45 us each),
+// so the longest tile bounds a small batch; more tiles cost a full chip a
+// set-up and p + 1 more flushed control rows each.  Forward and backward of
+// uneven batches of n surfaces, kernel time in us by rows per tile (equal
+// parts; the last column 16384 points, up to 256 rows and more):
+//   n       48    56    64    72    80    96   256
+//   4096   488   465   467   460   467   474   465
+//   1024   171   179   184   183   197   211   271
+//   256    135   139   137   138   151   177   241
+//   64     110   110   110   110   108   153   206
+// (parts of 64 rows and a remainder: 469, 172, 135, 102).  The backward of one
+// bicubic 512 x 512 surface: 49 at 64 rows, 134 at 256.
+constexpr int kDefaultRows = 72;
+// What the built-in scratch's limit and the server count in.
+constexpr int kDefaultTilePts = 16384;
+
 int tile_rows(int nu_s, int nv_s, int target_pts) {
     const int cols = std::max(1, std::min(kWave, nv_s));
     const int rows = std::max(1, target_pts / cols);
@@ -170,9 +190,8 @@ int nurbs_ctx_set_knot_sigma(nurbs_ctx* ctx, float sigma) {
 
 int nurbs_ctx_set_tiling(nurbs_ctx* ctx, int fwd_tile_points, int bwd_tile_points) {
     if (!ctx) return fail(nullptr, NURBS_EINVAL, "ctx is NULL");
-    const int f = fwd_tile_points ? fwd_tile_points : 16384;
-    const int b = bwd_tile_points ? bwd_tile_points : 16384;
-    if (f < kWave || f > (1 << 22) || b < kWave || b > (1 << 22))
+    const int f = fwd_tile_points, b = bwd_tile_points;
+    if ((f && (f < kWave || f > (1 << 22))) || (b && (b < kWave || b > (1 << 22))))
         return fail(ctx, NURBS_EINVAL, "tile points must be in [64, 4194304] (or 0 for the default)");
     ctx->fwd_tile_pts = f;
     ctx->bwd_tile_pts = b;
@@ -201,23 +220,49 @@ int nurbs_ctx_device_info(nurbs_ctx* ctx, int* num_cus, int* wave_size) {
 // --------------------------------------------------------------------------
 namespace {
 
+int rows_bwd(const nurbs_ctx* c, int nu_s, int nv_s) {
+    if (c->bwd_tile_pts) return tile_rows(nu_s, nv_s, c->bwd_tile_pts);
+    const int parts = std::max(1, (nu_s + kDefaultRows / 2) / kDefaultRows);
+    return std::max(1, (nu_s + parts - 1) / parts);
+}
+
 struct UniformGeom {
     int ncb, nrb_f, rows_f, nrb_b, rows_b;
-    long long tiles_f, tiles_b;
-    size_t slot;
+    long long tiles_f;
+    int tiles_b;        // backward tiles of one surface
+    size_t slot;        // bytes of a backward tile's slot
+    int group;          // surfaces the backward takes at a time (its workspace holds their slots)
 };
+
+// Most workspace the backward's slots take unless one surface needs more.
+constexpr size_t kGroupBytes = size_t(1) << 30;
+
+// Rows of a forward tile when the caller set none.  A point's bits do not
+// depend on the tile it is in, so the rows may follow the batch: enough tiles
+// to give every SIMD four waves, 8 to 64 rows
+// each (a tile's set-up and first window cost about four rows).  One bicubic
+// 512 x 512 surface, 64 x 64 net: 8 rows 6.8 us, 256 rows 46 us; 256 surfaces
+// of 128 x 128: 16 rows 13.6 us, 64 rows 17.5, 128 rows 26; 1024 of 64 x 64:
+// 16 rows 13.4 us, 64 rows 15.4.
+int auto_rows_fwd(int cus, long long col_rows, int nu_s) {
+    const long long rows = col_rows / (16ll * cus);
+    return (int)std::max<long long>(1, std::min<long long>(nu_s, std::min(64ll, std::max(8ll, rows))));
+}
 
 UniformGeom uniform_geom(const nurbs_ctx* c, int B, int p, int q, int nu_c, int nv_c, int nu_s, int nv_s) {
     UniformGeom g;
     g.ncb = (nv_s + kWave - 1) / kWave;
     const long long cols = (long long)B * g.ncb;
-    g.rows_f = tile_rows(nu_s, nv_s, c->fwd_tile_pts);
-    g.rows_b = tile_rows(nu_s, nv_s, c->bwd_tile_pts);
+    g.rows_f = c->fwd_tile_pts ? tile_rows(nu_s, nv_s, c->fwd_tile_pts)
+                               : auto_rows_fwd(std::max(c->num_cus, 1), cols * nu_s, std::max(nu_s, 1));
+    g.rows_b = rows_bwd(c, nu_s, nv_s);
     g.nrb_f = (nu_s + g.rows_f - 1) / g.rows_f;
     g.nrb_b = (nu_s + g.rows_b - 1) / g.rows_b;
     g.tiles_f = cols * g.nrb_f;
-    g.tiles_b = cols * g.nrb_b;
+    g.tiles_b = g.ncb * g.nrb_b;
     g.slot = slot_bytes(p, q, nu_c, nv_c, g.rows_b);
+    const size_t one = std::max<size_t>(1, (size_t)g.tiles_b * g.slot);
+    g.group = (int)std::max<long long>(1, std::min<long long>(B, (long long)(kGroupBytes / one)));
     return g;
 }
 
@@ -244,7 +289,7 @@ UniformArgs make_uargs(const nurbs_ctx* ctx, const UniformGeom& g, bool bwd, int
     a.ncb = g.ncb;
     a.nrb = bwd ? g.nrb_b : g.nrb_f;
     a.rows = bwd ? g.rows_b : g.rows_f;
-    a.ntiles = (int)(bwd ? g.tiles_b : g.tiles_f);
+    a.ntiles = bwd ? B * g.tiles_b : (int)g.tiles_f;
     a.flags = ctx->flags;
     a.err = (ctx->flags & NURBS_VALIDATE) ? reinterpret_cast<int*>(ws) : nullptr;
     a.tab_u = a.tab_v = nullptr;
@@ -265,7 +310,7 @@ int nurbs_surface_ws_bytes(nurbs_ctx* ctx, int B, int p, int q, int nu_c, int nv
         return NURBS_OK;
     }
     const UniformGeom g = uniform_geom(ctx, B, p, q, nu_c, nv_c, nu_s, nv_s);
-    *out = kWsHeader + (size_t)g.tiles_b * g.slot;
+    *out = kWsHeader + (size_t)g.group * g.tiles_b * g.slot;
     return NURBS_OK;
 }
 
@@ -328,13 +373,72 @@ hipError_t launch_uniform_gather(const nurbs_ctx* ctx, hipStream_t st, const Uni
     return q <= 5 ? launch_uniform_gat_d5(st, a, p, q, slots, slot_sz, ctx->num_cus)
                   : launch_uniform_gat_d7(st, a, p, q, slots, slot_sz, ctx->num_cus);
 }
+
+// The workspace has to hold the slots of a group of surfaces; `fit` takes
+// smaller groups instead where it does not (the built-in scratch).
+int check_bwd_ws(nurbs_ctx* ctx, UniformGeom& g, int B, int nu_c, int nv_c, const void* ws, size_t ws_bytes, bool fit) {
+    const size_t one = (size_t)g.tiles_b * g.slot;
+    if (fit && ws_bytes > kWsHeader)
+        g.group = (int)std::max<size_t>(1, std::min<size_t>(g.group, (ws_bytes - kWsHeader) / std::max<size_t>(1, one)));
+    const size_t need = kWsHeader + g.group * one;
+    if (!ws || ws_bytes < need) return fail(ctx, NURBS_EWORKSPACE, "workspace too small: need " + std::to_string(need));
+    if ((long long)g.group * g.tiles_b > (1ll << 30) || (long long)B * fin_parts(nu_c, nv_c) > (1ll << 30) ||
+        (long long)g.group * (2 + (nu_c * nv_c + kWave - 1) / kWave) > (1ll << 30))
+        return fail(ctx, NURBS_EINVAL, "batch too large");
+    return NURBS_OK;
+}
+
+// Row loop, gather and finalize of B surfaces, a group at a time (a.B and the
+// pointers of `a` are the batch's first surface's).
+hipError_t launch_uniform_backward(const nurbs_ctx* ctx, hipStream_t st, const UniformGeom& g, const UniformArgs& a0,
+                                   int B, int p, int q, const float* gpts, float* gc, float* gw, float* gku,
+                                   float* gkv, unsigned mask, char* slots) {
+    const size_t cp = (size_t)a0.nu_c * a0.nv_c, nU = a0.nu_c + p + 1, nV = a0.nv_c + q + 1;
+    for (int b0 = 0; b0 < B; b0 += g.group) {
+        UniformArgs a = a0;
+        const size_t b = (size_t)b0;
+        a.B = std::min(g.group, B - b0);
+        a.ntiles = a.B * g.tiles_b;
+        a.ctrl += b * cp * 3;
+        a.w += b * cp;
+        a.ku += b * nU;
+        a.kv += b * nV;
+        if (!a.uv_shared) {
+            a.us += b * a.nu_s;
+            a.vs += b * a.nv_s;
+        }
+        if (a.tab_u) {
+            a.tab_u += b * a.tab_u_stride;
+            a.tab_v += b * a.tab_v_stride;
+        }
+        const float* gp = gpts + b * a.nu_s * a.nv_s * 3;
+        float* c = gc ? gc + b * cp * 3 : nullptr;
+        float* w = gw ? gw + b * cp : nullptr;
+        float* u = gku ? gku + b * nU : nullptr;
+        float* v = gkv ? gkv + b * nV : nullptr;
+        const dim3 grid((unsigned)((a.ntiles + kWavesPerWG - 1) / kWavesPerWG));
+        hipError_t e = hipErrorInvalidValue;
+        switch (p) {
+#define ND_CASE(P)                                                                                        \
+    case P:                                                                                               \
+        e = launch_uniform_bwd_p##P(q, grid, st, a, gp, slots, g.slot, mask);                             \
+        if (e == hipSuccess) e = launch_uniform_gather(ctx, st, a, p, q, slots, g.slot, mask);            \
+        if (e == hipSuccess) e = launch_uniform_fin_p##P(q, st, a, slots, g.slot, c, w, u, v, mask);      \
+        break;
+            ND_CASE(1) ND_CASE(2) ND_CASE(3) ND_CASE(4) ND_CASE(5) ND_CASE(6) ND_CASE(7)
+#undef ND_CASE
+        }
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
 }  // namespace
 
-int nurbs_surface_bwd(nurbs_ctx* ctx, int B, int p, int q, int nu_c, int nv_c, const float* ctrl,
-                      const float* w, const float* ku, const float* kv, int nu_s, int nv_s, const float* us,
-                      const float* vs, int uv_shared, const float* grad_pts, float* grad_ctrl, float* grad_w,
-                      float* grad_ku, float* grad_kv, unsigned grad_mask, void* ws, size_t ws_bytes,
-                      void* stream) {
+namespace {
+int surface_bwd(nurbs_ctx* ctx, int B, int p, int q, int nu_c, int nv_c, const float* ctrl, const float* w,
+                const float* ku, const float* kv, int nu_s, int nv_s, const float* us, const float* vs, int uv_shared,
+                const float* grad_pts, float* grad_ctrl, float* grad_w, float* grad_ku, float* grad_kv,
+                unsigned grad_mask, void* ws, size_t ws_bytes, bool fit, void* stream) {
     int rc = uniform_common(ctx, B, p, q, nu_c, nv_c, nu_s, nv_s);
     if (rc) return rc;
     if (grad_mask & ~NURBS_GRAD_ALL) return fail(ctx, NURBS_EINVAL, "unknown gradient bits");
@@ -356,32 +460,24 @@ int nurbs_surface_bwd(nurbs_ctx* ctx, int B, int p, int q, int nu_c, int nv_c, c
     }
     if (!ctrl || !w || !ku || !kv || !us || !vs) return fail(ctx, NURBS_EINVAL, "NULL array");
     if (!grad_pts) return fail(ctx, NURBS_EINVAL, "NULL grad_pts");
-    const UniformGeom g = uniform_geom(ctx, B, p, q, nu_c, nv_c, nu_s, nv_s);
-    const size_t need = kWsHeader + (size_t)g.tiles_b * g.slot;
-    if (!ws || ws_bytes < need) return fail(ctx, NURBS_EWORKSPACE, "workspace too small: need " + std::to_string(need));
-    if (g.tiles_b > (1ll << 30)) return fail(ctx, NURBS_EINVAL, "batch too large");
-    const long long fin_items = (long long)B * fin_parts(nu_c, nv_c);
-    if (fin_items > (1ll << 30)) return fail(ctx, NURBS_EINVAL, "batch too large");
-    UniformArgs a = make_uargs(ctx, g, true, B, nu_c, nv_c, nu_s, nv_s, ctrl, w, ku, kv, us, vs, uv_shared, ws);
-    char* slots = reinterpret_cast<char*>(ws) + kWsHeader;
-    const dim3 grid((unsigned)((g.tiles_b + kWavesPerWG - 1) / kWavesPerWG));
-    hipError_t e = hipErrorInvalidValue;
-    switch (p) {
-#define ND_CASE(P)                                                                                        \
-    case P:                                                                                               \
-        e = launch_uniform_bwd_p##P(q, grid, st, a, grad_pts, slots, g.slot, grad_mask);                  \
-        if (e == hipSuccess) e = launch_uniform_gather(ctx, st, a, p, q, slots, g.slot, grad_mask);      \
-        if (e == hipSuccess)                                                                              \
-            e = launch_uniform_fin_p##P(q, dim3((fin_items + kWavesPerWG - 1) / kWavesPerWG), st, a, slots,  \
-                                        g.slot,                                                           \
-                                        grad_ctrl, grad_w, grad_ku,                                       \
-                                        grad_kv, grad_mask);                                              \
-        break;
-        ND_CASE(1) ND_CASE(2) ND_CASE(3) ND_CASE(4) ND_CASE(5) ND_CASE(6) ND_CASE(7)
-#undef ND_CASE
-    }
+    UniformGeom g = uniform_geom(ctx, B, p, q, nu_c, nv_c, nu_s, nv_s);
+    rc = check_bwd_ws(ctx, g, B, nu_c, nv_c, ws, ws_bytes, fit);
+    if (rc) return rc;
+    const UniformArgs a = make_uargs(ctx, g, true, 0, nu_c, nv_c, nu_s, nv_s, ctrl, w, ku, kv, us, vs, uv_shared, ws);
+    const hipError_t e = launch_uniform_backward(ctx, st, g, a, B, p, q, grad_pts, grad_ctrl, grad_w, grad_ku, grad_kv,
+                                                 grad_mask, reinterpret_cast<char*>(ws) + kWsHeader);
     if (e != hipSuccess) return hip_fail(ctx, e, "launch backward");
     return NURBS_OK;
+}
+}  // namespace
+
+int nurbs_surface_bwd(nurbs_ctx* ctx, int B, int p, int q, int nu_c, int nv_c, const float* ctrl,
+                      const float* w, const float* ku, const float* kv, int nu_s, int nv_s, const float* us,
+                      const float* vs, int uv_shared, const float* grad_pts, float* grad_ctrl, float* grad_w,
+                      float* grad_ku, float* grad_kv, unsigned grad_mask, void* ws, size_t ws_bytes,
+                      void* stream) {
+    return surface_bwd(ctx, B, p, q, nu_c, nv_c, ctrl, w, ku, kv, nu_s, nv_s, us, vs, uv_shared, grad_pts, grad_ctrl,
+                       grad_w, grad_ku, grad_kv, grad_mask, ws, ws_bytes, false, stream);
 }
 
 // --------------------------------------------------------------------------
@@ -469,29 +565,13 @@ int nurbs_surface_bwd_tab(nurbs_ctx* ctx, int B, int p, int q, int nu_c, int nv_
     }
     if (!ctrl || !w || !ku || !kv || !us || !vs) return fail(ctx, NURBS_EINVAL, "NULL array");
     if (!grad_pts || !tab_u || !tab_v) return fail(ctx, NURBS_EINVAL, "NULL grad_pts or table");
-    const UniformGeom g = uniform_geom(ctx, B, p, q, nu_c, nv_c, nu_s, nv_s);
-    const size_t need = kWsHeader + (size_t)g.tiles_b * g.slot;
-    if (!ws || ws_bytes < need) return fail(ctx, NURBS_EWORKSPACE, "workspace too small: need " + std::to_string(need));
-    if (g.tiles_b > (1ll << 30)) return fail(ctx, NURBS_EINVAL, "batch too large");
-    const long long fin_items = (long long)B * fin_parts(nu_c, nv_c);
-    if (fin_items > (1ll << 30)) return fail(ctx, NURBS_EINVAL, "batch too large");
-    UniformArgs a = make_uargs(ctx, g, true, B, nu_c, nv_c, nu_s, nv_s, ctrl, w, ku, kv, us, vs, uv_shared, ws);
+    UniformGeom g = uniform_geom(ctx, B, p, q, nu_c, nv_c, nu_s, nv_s);
+    rc = check_bwd_ws(ctx, g, B, nu_c, nv_c, ws, ws_bytes, false);
+    if (rc) return rc;
+    UniformArgs a = make_uargs(ctx, g, true, 0, nu_c, nv_c, nu_s, nv_s, ctrl, w, ku, kv, us, vs, uv_shared, ws);
     bind_tables(a, p, q, tab_u, tab_v, tab_shared);
-    char* slots = reinterpret_cast<char*>(ws) + kWsHeader;
-    const dim3 grid((unsigned)((g.tiles_b + kWavesPerWG - 1) / kWavesPerWG));
-    hipError_t e = hipErrorInvalidValue;
-    switch (p) {
-#define ND_CASE(P)                                                                                        \
-    case P:                                                                                               \
-        e = launch_uniform_bwd_p##P(q, grid, st, a, grad_pts, slots, g.slot, grad_mask);                  \
-        if (e == hipSuccess) e = launch_uniform_gather(ctx, st, a, p, q, slots, g.slot, grad_mask);      \
-        if (e == hipSuccess)                                                                              \
-            e = launch_uniform_fin_p##P(q, dim3((fin_items + kWavesPerWG - 1) / kWavesPerWG), st, a, slots,  \
-                                        g.slot, grad_ctrl, grad_w, nullptr, nullptr, grad_mask);          \
-        break;
-        ND_CASE(1) ND_CASE(2) ND_CASE(3) ND_CASE(4) ND_CASE(5) ND_CASE(6) ND_CASE(7)
-#undef ND_CASE
-    }
+    const hipError_t e = launch_uniform_backward(ctx, st, g, a, B, p, q, grad_pts, grad_ctrl, grad_w, nullptr, nullptr,
+                                                 grad_mask, reinterpret_cast<char*>(ws) + kWsHeader);
     if (e != hipSuccess) return hip_fail(ctx, e, "launch backward (tables)");
     return NURBS_OK;
 }
@@ -546,9 +626,11 @@ int nurbs_surface_bwd_noalloc(nurbs_ctx* ctx, int B, int p, int q, int nu_c, int
         return fail(ctx, NURBS_EUNSUPPORTED,
                     "nurbs_surface_bwd_noalloc runs no device-side data checks; clear NURBS_VALIDATE");
     if (grad_mask & ~NURBS_GRAD_ALL) return fail(ctx, NURBS_EINVAL, "unknown gradient bits");
-    size_t need = 0;
-    rc = nurbs_surface_ws_bytes(ctx, B, p, q, nu_c, nv_c, nu_s, nv_s, grad_mask, &need);
-    if (rc) return rc;
+    // the limit counts every surface's slots in tiles of 16384 points (or the
+    // caller's), whatever tiles and groups the call then takes
+    const int rows = tile_rows(nu_s, nv_s, ctx->bwd_tile_pts ? ctx->bwd_tile_pts : kDefaultTilePts);
+    const size_t tiles = (size_t)B * ((nv_s + kWave - 1) / kWave) * ((nu_s + rows - 1) / rows);
+    const size_t need = grad_mask ? kWsHeader + tiles * slot_bytes(p, q, nu_c, nv_c, rows) : 0;
     if (need > kNoAllocScratchBytes)
         return fail(ctx, NURBS_EWORKSPACE,
                     "this backward needs " + std::to_string(need) + " bytes of scratch; the built-in scratch holds " +
@@ -559,8 +641,8 @@ int nurbs_surface_bwd_noalloc(nurbs_ctx* ctx, int B, int p, int q, int nu_c, int
     // same kernels as nurbs_surface_bwd; every slot the finalize reads is
     // written by the backward kernel of the same call, and no error word is
     // used (NURBS_VALIDATE is refused), so nothing needs clearing first
-    return nurbs_surface_bwd(ctx, B, p, q, nu_c, nv_c, ctrl, w, ku, kv, nu_s, nv_s, us, vs, uv_shared, grad_pts,
-                             grad_ctrl, grad_w, grad_ku, grad_kv, grad_mask, ws, kNoAllocScratchBytes, stream);
+    return surface_bwd(ctx, B, p, q, nu_c, nv_c, ctrl, w, ku, kv, nu_s, nv_s, us, vs, uv_shared, grad_pts, grad_ctrl,
+                       grad_w, grad_ku, grad_kv, grad_mask, ws, kNoAllocScratchBytes, true, stream);
 }
 
 // --------------------------------------------------------------------------
@@ -960,6 +1042,8 @@ int plan_build(nurbs_ctx* ctx, const nurbs_desc* host, int n, unsigned flags, nu
     std::vector<double> fcost, bcost, gcost;
     size_t slot_off = 0;
     const int cus = std::max(ctx->num_cus, 1);
+    long long col_rows = 0;  // sample rows of all 64-column blocks
+    for (int s = 0; s < n; ++s) col_rows += (long long)((pl->host[s].nv_s + kWave - 1) / kWave) * pl->host[s].nu_s;
     for (int s = 0; s < n; ++s) {
         const nurbs_desc& d = pl->host[s];
         DevDesc& x = dd[s];
@@ -968,8 +1052,9 @@ int plan_build(nurbs_ctx* ctx, const nurbs_desc* host, int n, unsigned flags, nu
         x.us_off = d.us_off; x.vs_off = d.vs_off; x.pts_off = d.pts_off;
         x.pad = 0;
         const int ncb = (d.nv_s + kWave - 1) / kWave;
-        const int rf = tile_rows(d.nu_s, d.nv_s, ctx->fwd_tile_pts);
-        const int rb = tile_rows(d.nu_s, d.nv_s, ctx->bwd_tile_pts);
+        const int rf = ctx->fwd_tile_pts ? tile_rows(d.nu_s, d.nv_s, ctx->fwd_tile_pts)
+                                         : auto_rows_fwd(cus, col_rows, std::max(d.nu_s, 1));
+        const int rb = rows_bwd(ctx, d.nu_s, d.nv_s);
         x.rows = rb;
         x.tile_first = (int)bt.size();
         x.slot0 = (long long)(kPlanHeader + slot_off);

@@ -1076,13 +1076,11 @@ __device__ __forceinline__ void bwd_tile(const Surf& sg, int q, int col0, int ro
 // --------------------------------------------------------------------------
 // finalize: one wave per surface (kWavesPerWG surfaces per workgroup)
 // --------------------------------------------------------------------------
-constexpr int kFinMaxTiles = 64;  // tile headers staged in LDS (more: read from global)
-constexpr int kFinCp = 4;         // control points per lane per pass (registers for six waves/SIMD)
+constexpr int kFinCp = 4;         // plans: control points per lane per pass (registers for six waves/SIMD)
 constexpr int kFinW = 2 * kMaxDeg + 2;
 
-struct FinLds {
+struct alignas(16) FinLds {
     float knots[kWG];
-    int4 hdr[kFinMaxTiles];
     float contrib[kWave * kFinW];  // per run head of the chunk, run sums of the knot-window adjoints
     short head_of[kWG];            // span - first span of the chunk -> head lane, or -1
 };
@@ -1111,16 +1109,19 @@ __device__ __forceinline__ TileRef surface_tile(const char* slot0, size_t stride
 
 // Knot gradient of one direction: for every sample x_a of the direction,
 // coef(a)[r] = dL/dN_{k_a-D+r}(x_a) is turned into per-knot adjoints
-// g_t(a) = d/dU_{k_a-D+t} by basis_knot_adjoint (t = 0..2D+1).  Samples come
+// g_t(a) = d/dU_{k_a-D+1+t} by span_adjoint (t = 0..2D-1).  Samples come
 // 64 at a time; within a chunk, the samples of one span form a run of lanes
 // (spans are non-decreasing), so each g_t is first summed over its run by a
 // DPP segmented scan.  Knot kk then takes, for each t, the run sum of the
-// span kk + D - t (one LDS read through the run-head table), accumulating
+// span kk + D - 1 - t (one LDS read through the run-head table), accumulating
 // in FP64 in a fixed order (chunks, then t).
-template <int D, class CoefAt>
+//
+// NW > 1 waves of a workgroup (all of them) take the chunks in turn, NW at a
+// time, and add their sums chunk by chunk, so the bits are those of one wave.
+template <int D, int NW, class CoefAt>
 __device__ __forceinline__ void knot_gradient(const float* __restrict__ Ug, int nc, const float* __restrict__ xs,
                                               int ns, CoefAt coef_at, float* __restrict__ gout, FinLds* L) {
-    constexpr int W = 2 * D + 2;
+    constexpr int W = 2 * D;
     const int lane = lane_id();
     const int nk = nc + D + 1;
     const int n = nc - 1;
@@ -1128,161 +1129,187 @@ __device__ __forceinline__ void knot_gradient(const float* __restrict__ Ug, int 
     for (int i = lane; i < nk; i += kWave) L->knots[i] = Ug[i];
     wave_lds_sync();
     const float* U = L->knots;
-    double acc[kWG / kWave];
+    // one wave: knots lane + 64 m; several: the chunk's sums of those knots
+    constexpr int kM = kWG / kWave;
+    double acc[kM];
 #pragma unroll
-    for (int m = 0; m < kWG / kWave; ++m) acc[m] = 0.0;
-    for (int g0 = 0; g0 < ns; g0 += kWG) {
-        // the parameters of four chunks are fetched together, and each chunk's
-        // coefficients while the previous chunk is being worked on
-        float xv[kWG / kWave];
+    for (int m = 0; m < kM; ++m) acc[m] = 0.0;
+    double total = 0.0;  // NW > 1: of knot threadIdx.x
+    const int wv = NW > 1 ? (int)threadIdx.x / kWave : 0;
+    // the parameters of four chunks are fetched together, and each chunk's
+    // coefficients while the previous chunk is being worked on
+    for (int g0 = wv * kWave; g0 - wv * kWave < ns; g0 += kM * NW * kWave) {
+        float xv[kM];
 #pragma unroll
-        for (int c = 0; c < kWG / kWave; ++c) xv[c] = xs[min(g0 + c * kWave + lane, ns - 1)];
+        for (int c = 0; c < kM; ++c) xv[c] = xs[min(g0 + c * NW * kWave + lane, ns - 1)];
         float en[D + 1];
         coef_at(min(g0 + lane, ns - 1), en);
 #pragma unroll
-        for (int c = 0; c < kWG / kWave; ++c) {
-            const int a0 = g0 + c * kWave;
-            if (a0 >= ns) break;
+        for (int c = 0; c < kM; ++c) {
+            const int a0 = g0 + c * NW * kWave;
+            if (a0 - wv * kWave >= ns) break;  // the same for every wave
             const int a = a0 + lane;
             const int cnt = min(kWave, ns - a0);
             const bool valid = a < ns;
             float e[D + 1];
 #pragma unroll
             for (int r = 0; r <= D; ++r) e[r] = en[r];
-            if (c + 1 < kWG / kWave && a0 + kWave < ns) coef_at(min(a + kWave, ns - 1), en);
-            int k = 0;
-            float g[W];
+            if (c + 1 < kM && a0 - wv * kWave + NW * kWave < ns) coef_at(min(a + NW * kWave, ns - 1), en);
+            double sub[kM];
 #pragma unroll
-            for (int t = 0; t < W; ++t) g[t] = 0.0f;
-            if (valid) {
-                const float x = clamp_param(U, D, n, xv[c]);
-                k = find_span(U, D, n, x);
-                basis_knot_adjoint<D>(U, k, x, e, g);
-            }
-            const int kfirst = bcast_lane(k, 0);
-            const int nkeys = bcast_lane(k, cnt - 1) - kfirst + 1;
-            // lanes past the last sample get keys of their own (runs of one, adding zeros)
-            const int key = valid ? k - kfirst : 0x40000000 + lane;
-            const Runs rr = wave_runs(key);
-            // W = 2D is even: four values per scan while they last, then two
+            for (int m = 0; m < kM; ++m) sub[m] = 0.0;
+            if (NW == 1 || cnt > 0) {
+                int k = 0;
+                float g[W];
 #pragma unroll
-            for (int t = 0; t + 3 < W; t += 4) {
-                float4 x = make_float4(g[t], g[t + 1], g[t + 2], g[t + 3]);
-                seg_scan4(x, rr);
-                g[t] = x.x;
-                g[t + 1] = x.y;
-                g[t + 2] = x.z;
-                g[t + 3] = x.w;
-            }
-            if constexpr (W % 4 != 0) seg_scan2(g[W - 2], g[W - 1], rr);
-            for (int o = lane; o < nkeys; o += kWave) L->head_of[o] = (short)-1;
-            wave_lds_sync();
-            if (valid && rr.head) {
-                L->head_of[key] = (short)lane;
+                for (int t = 0; t < W; ++t) g[t] = 0.0f;
+                if (valid) {
+                    const float x = clamp_param(U, D, n, xv[c]);
+                    k = find_span(U, D, n, x);
+                    float K[2 * D], inv[D * (D + 1) / 2], N[D + 1], st[D * (D + 1) / 2];
 #pragma unroll
-                for (int t = 0; t < W; ++t) L->contrib[lane * W + t] = g[t];
-            }
-            wave_lds_sync();
+                    for (int t = 0; t < 2 * D; ++t) K[t] = U[k - D + 1 + t];
+                    span_inv<D>(K, inv);
+                    span_basis<D>(K, inv, x, N, st);
+                    span_adjoint<D>(K, inv, x, st, e, g);
+                }
+                const int kfirst = bcast_lane(k, 0);
+                const int nkeys = bcast_lane(k, cnt - 1) - kfirst + 1;
+                // lanes past the last sample get keys of their own (runs of one, adding zeros)
+                const int key = valid ? k - kfirst : 0x40000000 + lane;
+                const Runs rr = wave_runs(key);
+                // W = 2D is even: four values per scan while they last, then two
 #pragma unroll
-            for (int m = 0; m < kWG / kWave; ++m) {
-                if (m * kWave >= nk) break;
-                const int kk = lane + m * kWave;
-                if (kk < nk) {
+                for (int t = 0; t + 3 < W; t += 4) {
+                    float4 x = make_float4(g[t], g[t + 1], g[t + 2], g[t + 3]);
+                    seg_scan4(x, rr);
+                    g[t] = x.x;
+                    g[t + 1] = x.y;
+                    g[t + 2] = x.z;
+                    g[t + 3] = x.w;
+                }
+                if constexpr (W % 4 != 0) seg_scan2(g[W - 2], g[W - 1], rr);
+                for (int o = lane; o < nkeys; o += kWave) L->head_of[o] = (short)-1;
+                wave_lds_sync();
+                if (valid && rr.head) {
+                    L->head_of[key] = (short)lane;
 #pragma unroll
-                    for (int t = 0; t < W; ++t) {
-                        const int o = kk + D - t - kfirst;
-                        const int hl = (o >= 0 && o < nkeys) ? (int)L->head_of[o] : -1;
-                        if (hl >= 0) acc[m] += (double)L->contrib[hl * W + t];
+                    for (int t = 0; t < W; ++t) L->contrib[lane * W + t] = g[t];
+                }
+                wave_lds_sync();
+#pragma unroll
+                for (int m = 0; m < kM; ++m) {
+                    if (m * kWave >= nk) break;
+                    const int kk = lane + m * kWave;
+                    if (kk < nk) {
+#pragma unroll
+                        for (int t = 0; t < W; ++t) {
+                            const int o = kk + D - 1 - t - kfirst;
+                            const int hl = (o >= 0 && o < nkeys) ? (int)L->head_of[o] : -1;
+                            if (hl >= 0) sub[m] += (double)L->contrib[hl * W + t];
+                        }
                     }
                 }
+                wave_lds_sync();
             }
-            wave_lds_sync();
+            if constexpr (NW == 1) {
+#pragma unroll
+                for (int m = 0; m < kM; ++m) acc[m] += sub[m];
+            } else {
+                static_assert(sizeof(L->contrib) >= sizeof(double) * kWG, "a chunk's knot sums fit");
+                double* mine = reinterpret_cast<double*>(L->contrib);
+#pragma unroll
+                for (int m = 0; m < kM; ++m) mine[lane + m * kWave] = sub[m];
+                __syncthreads();
+                const FinLds* first = L - wv;
+#pragma unroll
+                for (int w = 0; w < NW; ++w)
+                    total += reinterpret_cast<const double*>(first[w].contrib)[threadIdx.x];
+                __syncthreads();
+            }
         }
     }
+    if constexpr (NW == 1) {
 #pragma unroll
-    for (int m = 0; m < kWG / kWave; ++m) {
-        const int kk = lane + m * kWave;
-        if (kk < nk) gout[kk] = (float)acc[m];
+        for (int m = 0; m < kM; ++m) {
+            const int kk = lane + m * kWave;
+            if (kk < nk) gout[kk] = (float)acc[m];
+        }
+    } else {
+        static_assert(NW * kWave == kWG, "a thread to a knot");
+        if ((int)threadIdx.x < nk) gout[threadIdx.x] = (float)total;
     }
 }
 
 // Finalize work of one surface, in parts that can run on different waves:
 //   kFinPW + c : dL/dP, dL/dw of control points [c * kFinChunk, (c + 1) * kFinChunk)
 //   kFinKU     : dL/dU;   kFinKV : dL/dV.
-constexpr int kFinChunk = kWave * kFinCp;  // control points per dP/dW part
+constexpr int kFinChunk = kWave * kFinCp;  // control points per dP/dW part of a plan
 constexpr int kFinKU = 0, kFinKV = 1, kFinPW = 2;
 
-// Sum of the tile rectangles over this lane's control points of one chunk,
-// tiles in fixed order, two tiles' loads in flight at a time.
-template <class TileAt>
-__device__ __forceinline__ void fin_pw_chunk(const Surf& s, int ntiles, TileAt tile_at, int chunk,
-                                             float* __restrict__ gctrl, float* __restrict__ gw, unsigned mask,
-                                             FinLds* L) {
+// Sum of the tile rectangles over CP * 64 control points from base on, CP per
+// lane, in tile order, FLY tiles' loads in flight at a time.  The lanes look
+// at 64 tiles' headers at once; only tiles whose rectangle meets the chunk's
+// rows and columns are read (a tile of a few sample rows touches a few
+// control rows).
+template <int CP, int FLY, class TileAt>
+__device__ __forceinline__ void fin_pw_chunk(const Surf& s, int ntiles, TileAt tile_at, int base,
+                                             float* __restrict__ gctrl, float* __restrict__ gw, unsigned mask) {
     const int lane = lane_id();
-    const bool hdr_lds = ntiles <= kFinMaxTiles;
-    if (hdr_lds)
-        for (int t = lane; t < ntiles; t += kWave) L->hdr[t] = *reinterpret_cast<const int4*>(tile_at(t).slot);
-    wave_lds_sync();
     const int ncp = s.nu_c * s.nv_c;
-    const int base = chunk * kFinChunk;
-    float4 acc[kFinCp];
-    int ii[kFinCp], jj[kFinCp];
+    float4 acc[CP];
+    int ii[CP], jj[CP];
 #pragma unroll
-    for (int c = 0; c < kFinCp; ++c) {
+    for (int c = 0; c < CP; ++c) {
         acc[c] = make_float4(0.f, 0.f, 0.f, 0.f);
         const int ij = base + c * kWave + lane;
         ii[c] = ij / s.nv_c;
         jj[c] = ij - ii[c] * s.nv_c;
     }
-    // v: the tile's rect entries; c: its frame origin.  The header comes from
-    // LDS or from the slot, in two compiled paths (one path with a run-time
-    // choice let the compiler merge both into generic-address loads).
-    auto load_tile = [&](auto hl, int t, float4 v[kFinCp], float4& c) {
-        const char* slot = tile_at(t).slot;
-        c = *reinterpret_cast<const float4*>(slot + 16);
-        int4 h;
-        if constexpr (decltype(hl)::value) h = L->hdr[t];
-        else h = *reinterpret_cast<const int4*>(slot);
-        const float4* rect = reinterpret_cast<const float4*>(slot + kSlotHead);
-        const int pitch = h.w - h.z + 1;
+    const int last = min(base + CP * kWave, ncp) - 1;
+    const int ilo = base / s.nv_c, ihi = last / s.nv_c;
+    const int jlo = ilo == ihi ? base - ilo * s.nv_c : 0, jhi = ilo == ihi ? last - ihi * s.nv_c : s.nv_c - 1;
+    for (int t0 = 0; t0 < ntiles; t0 += kWave) {
+        int4 h = make_int4(0, -1, 0, -1);
+        if (t0 + lane < ntiles) h = *reinterpret_cast<const int4*>(tile_at(t0 + lane).slot);
+        unsigned long long m = __ballot(h.x <= ihi && h.y >= ilo && h.z <= jhi && h.w >= jlo);
+        while (m) {
+            // v: a tile's rect entries; ct: its frame origin
+            float4 v[FLY][CP], ct[FLY];
 #pragma unroll
-        for (int c = 0; c < kFinCp; ++c) {
-            const int ij = base + c * kWave + lane;
-            const bool in = ij < ncp && ii[c] >= h.x && ii[c] <= h.y && jj[c] >= h.z && jj[c] <= h.w;
-            v[c] = in ? rect[(size_t)(ii[c] - h.x) * pitch + (jj[c] - h.z)] : make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-    };
-    // acc.w collects dL/dw - P . dL/dPw_xyz: the tile's rect w (its frame's
-    // dL/dw - (P - c) . dL/dPw_xyz) minus c . dL/dPw_xyz
-    auto add = [&](const float4 v[kFinCp], const float4 ct) {
+            for (int f = 0; f < FLY; ++f) {
+                const bool any = m != 0;
+                const int t = any ? __builtin_ctzll(m) : 0;
+                m &= m - 1;
+                const int i0 = bcast_lane(h.x, t), i1 = any ? bcast_lane(h.y, t) : -1;
+                const int j0 = bcast_lane(h.z, t), j1 = bcast_lane(h.w, t);
+                const char* slot = tile_at(t0 + t).slot;
+                ct[f] = *reinterpret_cast<const float4*>(slot + 16);
+                const float4* rect = reinterpret_cast<const float4*>(slot + kSlotHead);
 #pragma unroll
-        for (int c = 0; c < kFinCp; ++c) {
-            acc[c].x += v[c].x;
-            acc[c].y += v[c].y;
-            acc[c].z += v[c].z;
-            acc[c].w += v[c].w - (ct.x * v[c].x + ct.y * v[c].y + ct.z * v[c].z);
-        }
-    };
-    // two tiles' loads in flight at a time; sums still in tile order
-    auto sum_tiles = [&](auto hl) {
-        int t = 0;
-        for (; t + 1 < ntiles; t += 2) {
-            float4 va[kFinCp], vb[kFinCp], ca, cb;
-            load_tile(hl, t, va, ca);
-            load_tile(hl, t + 1, vb, cb);
-            add(va, ca);
-            add(vb, cb);
-        }
-        if (t < ntiles) {
-            float4 va[kFinCp], ca;
-            load_tile(hl, t, va, ca);
-            add(va, ca);
-        }
-    };
-    if (hdr_lds) sum_tiles(std::true_type{});
-    else sum_tiles(std::false_type{});
+                for (int c = 0; c < CP; ++c) {
+                    const int ij = base + c * kWave + lane;
+                    const bool in = ij < ncp && ii[c] >= i0 && ii[c] <= i1 && jj[c] >= j0 && jj[c] <= j1;
+                    v[f][c] = in ? rect[(size_t)(ii[c] - i0) * (j1 - j0 + 1) + (jj[c] - j0)]
+                                 : make_float4(0.f, 0.f, 0.f, 0.f);
+                }
+            }
+            // acc.w collects dL/dw - P . dL/dPw_xyz: the tile's rect w (its
+            // frame's dL/dw - (P - c) . dL/dPw_xyz) minus c . dL/dPw_xyz
 #pragma unroll
-    for (int c = 0; c < kFinCp; ++c) {
+            for (int f = 0; f < FLY; ++f)
+#pragma unroll
+                for (int c = 0; c < CP; ++c) {
+                    const float4 x = v[f][c];
+                    acc[c].x += x.x;
+                    acc[c].y += x.y;
+                    acc[c].z += x.z;
+                    acc[c].w += x.w - (ct[f].x * x.x + ct[f].y * x.y + ct[f].z * x.z);
+                }
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < CP; ++c) {
         const int ij = base + c * kWave + lane;
         if (ij >= ncp) continue;
         const float wt = s.w[ij];
@@ -1297,7 +1324,7 @@ __device__ __forceinline__ void fin_pw_chunk(const Surf& s, int ntiles, TileAt t
 }
 
 // dL/dU: e(a) = sum over the column blocks of a's row block.
-template <int P, class TileAt>
+template <int P, int NW, class TileAt>
 __device__ __forceinline__ void fin_knots_u(const Surf& s, int ntiles, TileAt tile_at, float* __restrict__ gku,
                                             FinLds* L) {
     const size_t rect_bytes = 16 * (size_t)s.nu_c * s.nv_c;
@@ -1307,6 +1334,7 @@ __device__ __forceinline__ void fin_knots_u(const Surf& s, int ntiles, TileAt ti
 #pragma unroll
         for (int r = 0; r <= P; ++r) e[r] = 0.0f;
         const int rb = a / rows;
+#pragma unroll(NW > 1 ? 4 : 1)
         for (int cb = 0; cb < ncb; ++cb) {
             const TileRef tr = tile_at(rb * ncb + cb);
             const float* ev = reinterpret_cast<const float*>(tr.slot + kSlotHead + rect_bytes) +
@@ -1315,12 +1343,12 @@ __device__ __forceinline__ void fin_knots_u(const Surf& s, int ntiles, TileAt ti
             for (int r = 0; r <= P; ++r) e[r] += ev[r];
         }
     };
-    knot_gradient<P>(s.ku, s.nu_c, s.us, s.nu_s, coef, gku, L);
+    knot_gradient<P, NW>(s.ku, s.nu_c, s.us, s.nu_s, coef, gku, L);
 }
 
 // dL/dV: f(b) = sum over the row blocks of b's column block (p, the degree
 // in u, only places f inside the slot).
-template <int Q, class TileAt>
+template <int Q, int NW, class TileAt>
 __device__ __forceinline__ void fin_knots_v(const Surf& s, int ntiles, TileAt tile_at, int p,
                                             float* __restrict__ gkv, FinLds* L) {
     const size_t rect_bytes = 16 * (size_t)s.nu_c * s.nv_c;
@@ -1330,6 +1358,8 @@ __device__ __forceinline__ void fin_knots_v(const Surf& s, int ntiles, TileAt ti
 #pragma unroll
         for (int h = 0; h <= Q; ++h) f[h] = 0.0f;
         const int cb = b / kWave;
+        // several row blocks' loads in flight; added in order
+#pragma unroll(NW > 1 ? (Q <= 3 ? 8 : 4) : 1)
         for (int rb = 0; rb < nrb; ++rb) {
             const TileRef tr = tile_at(rb * ncb + cb);
             const float* fv = reinterpret_cast<const float*>(
@@ -1338,7 +1368,7 @@ __device__ __forceinline__ void fin_knots_v(const Surf& s, int ntiles, TileAt ti
             for (int h = 0; h <= Q; ++h) f[h] += fv[(b - tr.col0) * (Q + 1) + h];
         }
     };
-    knot_gradient<Q>(s.kv, s.nv_c, s.vs, s.nv_s, coef, gkv, L);
+    knot_gradient<Q, NW>(s.kv, s.nv_c, s.vs, s.nv_s, coef, gkv, L);
 }
 
 // One finalize part (see kFinPW / kFinKU / kFinKV); the knot parts are
@@ -1349,13 +1379,14 @@ __device__ __forceinline__ void finalize_part(const Surf& s, int ntiles, TileAt 
                                               float* __restrict__ gku, float* __restrict__ gkv, unsigned mask,
                                               FinLds* L) {
     if (part >= kFinPW) {
-        if (mask & 3u) fin_pw_chunk(s, ntiles, tile_at, part - kFinPW, gctrl, gw, mask, L);
+        if (mask & 3u)
+            fin_pw_chunk<kFinCp, 2>(s, ntiles, tile_at, (part - kFinPW) * kFinChunk, gctrl, gw, mask);
     } else if (part == kFinKU) {
         if (!(mask & 4u)) return;
         switch (p) {
 #define ND_KU(D) \
     case D:      \
-        if constexpr (D <= DM) fin_knots_u<D>(s, ntiles, tile_at, gku, L); \
+        if constexpr (D <= DM) fin_knots_u<D, 1>(s, ntiles, tile_at, gku, L); \
         break;
             ND_KU(1) ND_KU(2) ND_KU(3) ND_KU(4) ND_KU(5) ND_KU(6) ND_KU(7)
 #undef ND_KU
@@ -1366,7 +1397,7 @@ __device__ __forceinline__ void finalize_part(const Surf& s, int ntiles, TileAt 
         switch (q) {
 #define ND_KV(D) \
     case D:      \
-        if constexpr (D <= DM) fin_knots_v<D>(s, ntiles, tile_at, p, gkv, L); \
+        if constexpr (D <= DM) fin_knots_v<D, 1>(s, ntiles, tile_at, p, gkv, L); \
         break;
             ND_KV(1) ND_KV(2) ND_KV(3) ND_KV(4) ND_KV(5) ND_KV(6) ND_KV(7)
 #undef ND_KV
@@ -1375,36 +1406,9 @@ __device__ __forceinline__ void finalize_part(const Surf& s, int ntiles, TileAt 
     }
 }
 
-// The same with both degrees known at compile time (uniform batches).
-template <int P, int Q, class TileAt>
-__device__ __forceinline__ void finalize_part_pq(const Surf& s, int ntiles, TileAt tile_at, int part,
-                                                 float* __restrict__ gctrl, float* __restrict__ gw,
-                                                 float* __restrict__ gku, float* __restrict__ gkv, unsigned mask,
-                                                 FinLds* L) {
-    if (part >= kFinPW) {
-        if (mask & 3u) fin_pw_chunk(s, ntiles, tile_at, part - kFinPW, gctrl, gw, mask, L);
-    } else if (part == kFinKU) {
-        if (mask & 4u) fin_knots_u<P>(s, ntiles, tile_at, gku, L);
-    } else {
-        if (mask & 8u) fin_knots_v<Q>(s, ntiles, tile_at, P, gkv, L);
-    }
-}
-
-// Number of parts of a surface's finalize.
+// Number of parts of a surface's finalize in a plan.
 __host__ __device__ inline int fin_parts(int nu_c, int nv_c) {
     return kFinPW + (nu_c * nv_c + kFinChunk - 1) / kFinChunk;
-}
-
-// All parts of one surface on one wave (uniform batches).
-template <int P, int Q, class TileAt>
-__device__ __forceinline__ void finalize_surface(const Surf& s, int ntiles, TileAt tile_at, float* __restrict__ gctrl,
-                                                 float* __restrict__ gw, float* __restrict__ gku,
-                                                 float* __restrict__ gkv, unsigned mask, FinLds* L) {
-    const int np = fin_parts(s.nu_c, s.nv_c);
-    for (int part = 0; part < np; ++part) {
-        finalize_part_pq<P, Q>(s, ntiles, tile_at, part, gctrl, gw, gku, gkv, mask, L);
-        wave_lds_sync();
-    }
 }
 
 // Surface s of a uniform batch (degrees p, q).

@@ -83,9 +83,9 @@ struct PlanArgs {
                                        float* pts, float* du, float* dv, float* nrm);                  \
     hipError_t launch_uniform_bwd_p##P(int q, dim3 grid, hipStream_t st, const UniformArgs& a,         \
                                        const float* gpts, char* slots, size_t slot_sz, unsigned mask); \
-    hipError_t launch_uniform_fin_p##P(int q, dim3 grid, hipStream_t st, const UniformArgs& a,         \
-                                       const char* slots, size_t slot_sz, float* gc, float* gw,        \
-                                       float* gku, float* gkv, unsigned mask);
+    hipError_t launch_uniform_fin_p##P(int q, hipStream_t st, const UniformArgs& a, const char* slots, \
+                                       size_t slot_sz, float* gc, float* gw, float* gku, float* gkv,   \
+                                       unsigned mask);
 ND_DECLARE_UNIFORM(1)
 ND_DECLARE_UNIFORM(2)
 ND_DECLARE_UNIFORM(3)

@@ -516,6 +516,10 @@ int nurbs_server_create(int device, const nurbs_desc* pool, int n_surf, const fl
     }
     int rc = nurbs_ctx_create(device, &s->ctx);
     if (rc == NURBS_OK) rc = nurbs_ctx_create(device, &s->qctx);
+    // tiles of 16384 points: the least workspace per request, so the most
+    // requests fit a slot's arena
+    if (rc == NURBS_OK) rc = nurbs_ctx_set_tiling(s->ctx, 16384, 16384);
+    if (rc == NURBS_OK) rc = nurbs_ctx_set_tiling(s->qctx, 16384, 16384);
     s->slots.resize(n_slots);
     for (Slot& sl : s->slots) {
         if (rc) break;
