@@ -35,11 +35,19 @@ def _ptr(t) -> int | None:
 
 
 def _stream(device) -> int:
-    return torch.cuda.current_stream(device).cuda_stream
+    # the raw handle itself: building the torch.cuda.Stream object that holds it
+    # took 2 us of a call, and 10 us on the autograd engine's thread, whose
+    # caches are cold (a 64 x 64 surface's forward and backward: 154 us on the
+    # host, of them 19 for the two stream look-ups)
+    index = device.index
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device() if index is None else index)
+
+
+_f32 = torch.float32
 
 
 def _need_cuda_f32(name, t):
-    if not (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype == torch.float32 and t.is_contiguous()):
+    if not (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype is _f32 and t.is_contiguous()):
         raise ValueError(f"{name} must be a contiguous float32 CUDA tensor")
 
 
@@ -125,14 +133,14 @@ def _uniform_shapes(ctrl, w, ku, kv, p, q, us, vs):
         ctrl, w, ku, kv = ctrl[None], w[None], ku[None], kv[None]
     if ctrl.dim() != 4 or ctrl.shape[-1] != 3:
         raise ValueError("ctrl must be [B, nu_c, nv_c, 3] or [nu_c, nv_c, 3]")
-    B, nu_c, nv_c = (int(x) for x in ctrl.shape[:3])
-    if tuple(w.shape) != (B, nu_c, nv_c):
+    B, nu_c, nv_c, _ = ctrl.shape
+    if w.shape != (B, nu_c, nv_c):
         raise ValueError("w must be [B, nu_c, nv_c]")
-    if tuple(ku.shape) != (B, nu_c + p + 1) or tuple(kv.shape) != (B, nv_c + q + 1):
+    if ku.shape != (B, nu_c + p + 1) or kv.shape != (B, nv_c + q + 1):
         raise ValueError("knot vectors must be [B, nu_c+p+1] and [B, nv_c+q+1]")
     if us.dim() == 1 and vs.dim() == 1:
         shared = 1
-        nu_s, nv_s = int(us.shape[0]), int(vs.shape[0])
+        nu_s, nv_s = us.shape[0], vs.shape[0]
     elif us.dim() == 2 and vs.dim() == 2 and us.shape[0] == B and vs.shape[0] == B:
         shared = 0
         nu_s, nv_s = int(us.shape[1]), int(vs.shape[1])
@@ -148,14 +156,12 @@ def surface_fwd(ctrl, w, ku, kv, p: int, q: int, us, vs, out=None, ctx: Context 
     ctx = ctx or context(ctrl.device.index)
     if out is None:
         out = torch.empty((B, nu_s, nv_s, 3), dtype=torch.float32, device=ctrl.device)
-    ws_n = ctypes.c_size_t()
-    _check(N.lib().nurbs_surface_ws_bytes(ctx.handle, B, p, q, nu_c, nv_c, nu_s, nv_s, 0,
-                                          ctypes.byref(ws_n)), ctx.handle)
-    ws = torch.zeros(ws_n.value, dtype=torch.uint8, device=ctrl.device) if ws_n.value else None
+    # a forward has a workspace for the data checks' error word only
+    ws = torch.zeros(256, dtype=torch.uint8, device=ctrl.device) if ctx.validate else None
     ctx.last_ws = ws
     _check(N.lib().nurbs_surface_fwd(ctx.handle, B, p, q, nu_c, nv_c, _ptr(ctrl), _ptr(w), _ptr(ku), _ptr(kv),
-                                     nu_s, nv_s, _ptr(us), _ptr(vs), shared, _ptr(out), _ptr(ws), ws_n.value,
-                                     _stream(ctrl.device)), ctx.handle)
+                                     nu_s, nv_s, _ptr(us), _ptr(vs), shared, _ptr(out), _ptr(ws),
+                                     0 if ws is None else 256, _stream(ctrl.device)), ctx.handle)
     return out[0] if squeeze else out
 
 
