@@ -858,27 +858,32 @@ int nurbs_surface_uv_bwd(nurbs_ctx* ctx, int B, int p, int q, int nu_c, int nv_c
 namespace {
 
 struct CdLayout {
-    size_t a, da, b, db, state, part, acc, pidx, pd2, total;
+    NnSplit sp, sq;  // both searches of a Chamfer distance, in one launch
+    NnSplit s1;      // the one search of nurbs_nearest
+    size_t a, b, state, part, acc, grp_p, d2_p, grp_q, d2_q, total;
 };
 
 // Workspace of nurbs_nearest / nurbs_chamfer: the 256-byte header, both
-// nearest-neighbour maps, the per-pair state and the per-range partials of
-// the larger of the two searches.
+// nearest-neighbour maps, the per-pair state and partials, the gradient's
+// accumulators and the per-range minima of the searches (nurbs_nearest's
+// in place of the first).
 CdLayout cd_layout(int B, int n, int m, int num_cus) {
     auto al = [](size_t x) { return (x + 255) & ~size_t(255); };
-    const NnSplit s1 = nn_split(B, n, m, num_cus), s2 = nn_split(B, m, n, num_cus);
-    const size_t part = std::max(s1.nranges > 1 ? (size_t)s1.nranges * n : 0, s2.nranges > 1 ? (size_t)s2.nranges * m : 0);
     CdLayout l;
+    l.sp = nn_split(B, n, m, 2, num_cus);
+    l.sq = nn_split(B, m, n, 2, num_cus);
+    l.s1 = nn_split(B, n, m, 1, num_cus);
+    const size_t rp = 4 * (size_t)B * n * std::max(l.sp.nranges, l.s1.nranges), rq = 4 * (size_t)B * m * l.sq.nranges;
     l.a = kWsHeader;
-    l.da = l.a + al(sizeof(int) * (size_t)B * n);
-    l.b = l.da + al(sizeof(float) * (size_t)B * n);
-    l.db = l.b + al(sizeof(int) * (size_t)B * m);
-    l.state = l.db + al(sizeof(float) * (size_t)B * m);
+    l.b = l.a + al(sizeof(int) * (size_t)B * n);
+    l.state = l.b + al(sizeof(int) * (size_t)B * m);
     l.part = l.state + al(cd_state_bytes() * (size_t)B);
     l.acc = l.part + al(cd_part_bytes(n, m) * (size_t)B);
-    l.pidx = l.acc + al(sizeof(unsigned long long) * 3 * (size_t)B * n);
-    l.pd2 = l.pidx + al(sizeof(int) * (size_t)B * part);
-    l.total = l.pd2 + al(sizeof(float) * (size_t)B * part);
+    l.grp_p = l.acc + al(sizeof(unsigned long long) * 3 * (size_t)B * n);
+    l.d2_p = l.grp_p + al(rp);
+    l.grp_q = l.d2_p + al(rp);
+    l.d2_q = l.grp_q + al(rq);
+    l.total = l.d2_q + al(rq);
     return l;
 }
 
@@ -908,13 +913,11 @@ int nurbs_nearest(nurbs_ctx* ctx, int B, int dim, const float* X, int n, const f
     if (B == 0) return NURBS_OK;
     if (!X || !Y || !idx || !d2) return fail(ctx, NURBS_EINVAL, "NULL array");
     const CdLayout l = cd_layout(B, n, m, ctx->num_cus);
-    const NnSplit sp = nn_split(B, n, m, ctx->num_cus);
     char* w = reinterpret_cast<char*>(ws);
     if (!ws || ws_bytes < l.total)
         return fail(ctx, NURBS_EWORKSPACE, "workspace too small: need " + std::to_string(l.total));
-    hipError_t e = launch_nn(dim, reinterpret_cast<hipStream_t>(stream), B, X, n, Y, m, sp, idx, d2,
-                             sp.nranges > 1 ? reinterpret_cast<int*>(w + l.pidx) : nullptr,
-                             sp.nranges > 1 ? reinterpret_cast<float*>(w + l.pd2) : nullptr);
+    hipError_t e = launch_nn(dim, reinterpret_cast<hipStream_t>(stream), B, X, n, Y, m, l.s1, idx, d2,
+                             reinterpret_cast<int*>(w + l.grp_p), reinterpret_cast<float*>(w + l.d2_p));
     return e ? hip_fail(ctx, e, "launch nearest") : NURBS_OK;
 }
 
@@ -927,17 +930,11 @@ int nurbs_chamfer(nurbs_ctx* ctx, int B, int dim, const float* P, int n, const f
     const CdLayout l = cd_layout(B, n, m, ctx->num_cus);
     if (!ws || ws_bytes < l.total) return fail(ctx, NURBS_EWORKSPACE, "workspace too small: need " + std::to_string(l.total));
     char* w = reinterpret_cast<char*>(ws);
-    int* a = reinterpret_cast<int*>(w + l.a);
-    float* da = reinterpret_cast<float*>(w + l.da);
-    int* bq = reinterpret_cast<int*>(w + l.b);
-    float* db = reinterpret_cast<float*>(w + l.db);
-    int* pidx = reinterpret_cast<int*>(w + l.pidx);
-    float* pd2 = reinterpret_cast<float*>(w + l.pd2);
-    hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    hipError_t e = launch_nn(dim, st, B, P, n, Q, m, nn_split(B, n, m, ctx->num_cus), a, da, pidx, pd2);
-    if (e == hipSuccess) e = launch_nn(dim, st, B, Q, m, P, n, nn_split(B, m, n, ctx->num_cus), bq, db, pidx, pd2);
-    if (e == hipSuccess)
-        e = launch_cd(dim, st, B, P, n, Q, m, a, da, bq, db, out, w + l.state, w + l.part, w + l.acc, grad_cd, grad_hd);
+    auto i32 = [&](size_t o) { return reinterpret_cast<int*>(w + o); };
+    auto f32 = [&](size_t o) { return reinterpret_cast<float*>(w + o); };
+    hipError_t e = launch_cd(dim, reinterpret_cast<hipStream_t>(stream), B, P, n, Q, m, l.sp, l.sq, i32(l.a), i32(l.b),
+                             i32(l.grp_p), f32(l.d2_p), i32(l.grp_q), f32(l.d2_q), out, w + l.state, w + l.part,
+                             w + l.acc, grad_cd, grad_hd);
     return e ? hip_fail(ctx, e, "launch chamfer") : NURBS_OK;
 }
 

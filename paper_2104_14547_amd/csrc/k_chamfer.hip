@@ -12,16 +12,24 @@
 // sums and gradients are then taken from the chosen pairs: distances in
 // FP64, gradients as FP32 unit vectors.
 //
-// Nearest neighbours (k_nn): brute force.  A workgroup takes 4 x 256 query
-// points (4 per lane, in registers) and one contiguous range of the target
-// set, staged through LDS 256 points at a time; every lane scans the
-// targets in increasing index order.  For small query sets the target set
-// is split into ranges over more workgroups, and k_nn_merge keeps, per
-// query, the first range with the strictly smallest d2 -- the same result
-// as one scan in index order.  Per query-target pair the work is 3
-// subtractions, 1 multiply, 2 FMAs, 1 compare and 2 selects: VALU bound.
+// Nearest neighbours: brute force over all pairs.  k_nn: a workgroup takes QL
+// x 256 query points (QL per lane, in registers) and one contiguous range of
+// the target set, staged through LDS 256 points at a time; every target read
+// is shared by the lane's QL queries.  It keeps the least d2 and the group of
+// kNnGroup consecutive targets it came from, not the index: a running minimum
+// (v_min3_f32, two distances to an instruction) instead of a compare and two
+// selects per pair.  k_nn_pick, one thread per query, takes the range with the
+// strictly smallest d2 (ranges and groups in index order, so ties go to the
+// smaller index) and finds the first target of its group with that d2: the
+// distances of one group again, from the same formula, so the same bits.  Both
+// directions of a Chamfer distance run in one launch.  What bounds it: VALU
+// issue, 3 subtractions, 1 multiply, 2 FMAs and half a minimum per pair (9
+// instructions when every pair carried its index).  16384 x 16384 points in
+// space, both directions: 84 us (two launches of 56 us before), the whole loss
+// with its gradients 88 us (132); 8 pairs of 1000 and 1531 points in the
+// plane 27 us (77: nine launches, and ranges too long to fill the chip).
 //
-// Gradient with respect to P (k_cd_scatter, k_cd_grad):
+// Gradient with respect to P (k_nn_pick, k_cd_grad):
 //   dCD/dP_i = (P_i - Q_a(i))/|.| + sum_{j : b(j) = i} (P_i - Q_j)/|.|
 //   dHD/dP_i = [i = i*] (P_i - Q_a(i*))/|.| + [i = b(j*)] (P_i - Q_j*)/|.|
 // (a: nearest target of each point, b: nearest point of each target,
@@ -37,9 +45,8 @@
 namespace nd {
 namespace {
 
-constexpr int kNnPerLane = 4;
-constexpr int kNnQueries = kWG * kNnPerLane;  // query points per workgroup
-constexpr int kNnTile = kWG;                  // targets per LDS stage
+constexpr int kNnTile = kWG;   // targets per LDS stage
+constexpr int kNnGroup = 16;   // targets whose least d2 is kept as one
 
 __device__ __forceinline__ float nn_d2(float px, float py, float pz, float4 q) {
     const float dx = px - q.x, dy = py - q.y, dz = pz - q.z;
@@ -52,113 +59,137 @@ __device__ __forceinline__ float4 load_pt(const float* __restrict__ X, long long
     return make_float4(p[0], p[1], DIM == 3 ? p[2] : 0.f, 0.f);
 }
 
-// For each query point X[b][i] the first index of its nearest point in
-// Y[b][j0 .. j1) and that squared distance.  Grid: (query blocks, ranges, B).
-template <int DIM>
-__global__ void __launch_bounds__(kWG) k_nn(const float* __restrict__ X, int n, const float* __restrict__ Y, int m,
-                                           int range, int* __restrict__ idx, float* __restrict__ d2, long long stride) {
-    __shared__ float4 tile[kNnTile];
-    const int b = blockIdx.z;
-    const int i0 = blockIdx.x * kNnQueries;
-    const int j0 = blockIdx.y * range, j1 = min(m, j0 + range);
-    const float* Xb = X + (long long)b * n * DIM;
-    const float* Yb = Y + (long long)b * m * DIM;
-    float px[kNnPerLane], py[kNnPerLane], pz[kNnPerLane], best[kNnPerLane];
-    int bi[kNnPerLane];
+// One direction of a search: each query point of X against all of Y.
+struct NnDir {
+    const float *X, *Y;
+    int n, m, ql, qblocks, range, nranges;
+    float* pd2;    // [B][nranges][n] least d2 of each range
+    int* pgrp;     // [B][nranges][n] the group it came from
+    int* idx;      // [B][n]
+    float* d2;     // [B][n]
+};
+
+// k_nn of one direction's workgroup (qb, r) of cloud pair b.
+template <int DIM, int QL>
+__device__ __forceinline__ void nn_range(const NnDir& s, int b, int qb, int r, float4* tile) {
+    const int i0 = qb * QL * kWG, j0 = r * s.range, j1 = min(s.m, j0 + s.range);
+    const float* Xb = s.X + (long long)b * s.n * DIM;
+    const float* Yb = s.Y + (long long)b * s.m * DIM;
+    float px[QL], py[QL], pz[QL], best[QL];
+    int bg[QL];
 #pragma unroll
-    for (int r = 0; r < kNnPerLane; ++r) {
-        const int i = i0 + r * kWG + (int)threadIdx.x;
-        const float4 p = i < n ? load_pt<DIM>(Xb, i) : make_float4(0.f, 0.f, 0.f, 0.f);
-        px[r] = p.x;
-        py[r] = p.y;
-        pz[r] = p.z;
-        best[r] = __builtin_inff();
-        bi[r] = -1;
+    for (int q = 0; q < QL; ++q) {
+        const float4 p = load_pt<DIM>(Xb, min(i0 + q * kWG + (int)threadIdx.x, s.n - 1));
+        px[q] = p.x;
+        py[q] = p.y;
+        pz[q] = p.z;
+        best[q] = __builtin_inff();
+        bg[q] = -1;
     }
     for (int t0 = j0; t0 < j1; t0 += kNnTile) {
         const int cnt = min(kNnTile, j1 - t0);
         __syncthreads();
-        if ((int)threadIdx.x < cnt) tile[threadIdx.x] = load_pt<DIM>(Yb, t0 + threadIdx.x);
+        // past the end: the last target again, whose distance changes no minimum
+        if ((int)threadIdx.x < (cnt + kNnGroup - 1) / kNnGroup * kNnGroup)
+            tile[threadIdx.x] = load_pt<DIM>(Yb, t0 + min((int)threadIdx.x, cnt - 1));
         __syncthreads();
-        if (cnt == kNnTile) {
-#pragma unroll 4
-            for (int j = 0; j < kNnTile; ++j) {
-                const float4 q = tile[j];
+        for (int g = 0; g * kNnGroup < cnt; ++g) {
+            float run[QL];
 #pragma unroll
-                for (int r = 0; r < kNnPerLane; ++r) {
-                    const float d = nn_d2(px[r], py[r], pz[r], q);
-                    if (d < best[r]) {
-                        best[r] = d;
-                        bi[r] = t0 + j;
-                    }
-                }
-            }
-        } else {
-            for (int j = 0; j < cnt; ++j) {
-                const float4 q = tile[j];
+            for (int q = 0; q < QL; ++q) run[q] = __builtin_inff();
 #pragma unroll
-                for (int r = 0; r < kNnPerLane; ++r) {
-                    const float d = nn_d2(px[r], py[r], pz[r], q);
-                    if (d < best[r]) {
-                        best[r] = d;
-                        bi[r] = t0 + j;
-                    }
-                }
+            for (int j = 0; j < kNnGroup; j += 2) {
+                const float4 y0 = tile[g * kNnGroup + j], y1 = tile[g * kNnGroup + j + 1];
+#pragma unroll
+                for (int q = 0; q < QL; ++q)
+                    run[q] = fminf(fminf(run[q], nn_d2(px[q], py[q], pz[q], y0)), nn_d2(px[q], py[q], pz[q], y1));
             }
+#pragma unroll
+            for (int q = 0; q < QL; ++q)
+                if (run[q] < best[q]) {
+                    best[q] = run[q];
+                    bg[q] = t0 / kNnGroup + g;
+                }
         }
     }
-    // no distance below +inf (or only NaN) in the range: its first target,
-    // as an ordered scan that starts from the first target would keep
-    const long long o = (long long)b * stride + (long long)blockIdx.y * n;
+    const long long o = ((long long)b * s.nranges + r) * s.n;
 #pragma unroll
-    for (int r = 0; r < kNnPerLane; ++r) {
-        const int i = i0 + r * kWG + (int)threadIdx.x;
-        if (i < n) {
-            const bool none = bi[r] < 0;
-            idx[o + i] = none ? j0 : bi[r];
-            d2[o + i] = none ? nn_d2(px[r], py[r], pz[r], load_pt<DIM>(Yb, j0)) : best[r];
+    for (int q = 0; q < QL; ++q) {
+        const int i = i0 + q * kWG + (int)threadIdx.x;
+        if (i < s.n) {
+            s.pd2[o + i] = best[q];
+            s.pgrp[o + i] = bg[q];
         }
     }
 }
 
-// Per query, the first range whose d2 is strictly smallest (ranges in index
-// order, so ties go to the smaller target index, as in one ordered scan).
-__global__ void __launch_bounds__(kWG) k_nn_merge(const int* __restrict__ pidx, const float* __restrict__ pd2,
-                                                 int n, int nranges, long long stride, int B,
-                                                 int* __restrict__ idx, float* __restrict__ d2) {
-    const long long t = (long long)blockIdx.x * kWG + threadIdx.x;
-    if (t >= (long long)B * n) return;
-    const int b = (int)(t / n), i = (int)(t - (long long)b * n);
-    const long long o = (long long)b * stride + i;
-    float best = pd2[o];
-    int bi = pidx[o];
-    // eight ranges' partials loaded together, then compared in range order
+// Grid: (workgroups of both directions, B).  zero: nzero 64-bit words cleared
+// on the way (the gradient's accumulators, used by the next kernel).
+template <int DIM>
+__global__ void __launch_bounds__(kWG) k_nn(NnDir s0, NnDir s1, unsigned long long* __restrict__ zero,
+                                           long long nzero) {
+    __shared__ float4 tile[kNnTile];
+    for (long long i = ((long long)blockIdx.y * gridDim.x + blockIdx.x) * kWG + threadIdx.x; i < nzero;
+         i += (long long)gridDim.x * gridDim.y * kWG)
+        zero[i] = 0ull;
+    const int first = s0.qblocks * s0.nranges;
+    const bool second = (int)blockIdx.x >= first;
+    const NnDir& s = second ? s1 : s0;
+    const int w = (int)blockIdx.x - (second ? first : 0);
+    const int qb = w / s.nranges, r = w - qb * s.nranges;
+    if (s.ql == 4) nn_range<DIM, 4>(s, blockIdx.y, qb, r, tile);
+    else if (s.ql == 2) nn_range<DIM, 2>(s, blockIdx.y, qb, r, tile);
+    else nn_range<DIM, 1>(s, blockIdx.y, qb, r, tile);
+}
+
+// The nearest target of query i: index and d2 (see the top of the file).
+template <int DIM>
+__device__ __forceinline__ int nn_pick(const NnDir& s, int b, int i, float* d2) {
+    const long long o = (long long)b * s.nranges * s.n + i;
+    float best = __builtin_inff();
+    int br = -1;
+    // eight ranges' minima loaded together, then compared in range order
     constexpr int kU = 8;
-    int r = 1;
-    for (; r + kU <= nranges; r += kU) {
+    for (int r0 = 0; r0 < s.nranges; r0 += kU) {
         float d[kU];
-        int ix[kU];
 #pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            d[u] = pd2[o + (long long)(r + u) * n];
-            ix[u] = pidx[o + (long long)(r + u) * n];
-        }
+        for (int u = 0; u < kU; ++u)
+            d[u] = r0 + u < s.nranges ? s.pd2[o + (long long)(r0 + u) * s.n] : __builtin_inff();
 #pragma unroll
         for (int u = 0; u < kU; ++u)
             if (d[u] < best) {
                 best = d[u];
-                bi = ix[u];
+                br = r0 + u;
             }
     }
-    for (; r < nranges; ++r) {
-        const float d = pd2[o + (long long)r * n];
-        if (d < best) {
-            best = d;
-            bi = pidx[o + (long long)r * n];
+    const float* Yb = s.Y + (long long)b * s.m * DIM;
+    const float4 p = load_pt<DIM>(s.X + (long long)b * s.n * DIM, i);
+    int bi = 0;
+    if (br < 0) {
+        // no distance below +inf (or only NaN): the first target, as an
+        // ordered scan that starts from it would keep
+        best = nn_d2(p.x, p.y, p.z, load_pt<DIM>(Yb, 0));
+    } else {
+        const int j0 = s.pgrp[o + (long long)br * s.n] * kNnGroup;
+#pragma unroll
+        for (int j = kNnGroup - 1; j >= 0; --j) {
+            const int k = min(j0 + j, s.m - 1);
+            if (nn_d2(p.x, p.y, p.z, load_pt<DIM>(Yb, k)) == best) bi = k;
         }
     }
-    idx[t] = bi;
-    d2[t] = best;
+    *d2 = best;
+    return bi;
+}
+
+// nurbs_nearest: one thread per query.
+template <int DIM>
+__global__ void __launch_bounds__(kWG) k_nn_pick(NnDir s) {
+    const int b = blockIdx.y, i = blockIdx.x * kWG + threadIdx.x;
+    if (i >= s.n) return;
+    float d2;
+    const int bi = nn_pick<DIM>(s, b, i, &d2);
+    s.idx[(long long)b * s.n + i] = bi;
+    s.d2[(long long)b * s.n + i] = d2;
 }
 
 // FP64 distance of a chosen pair and the FP32 unit vector from Y to X.
@@ -177,18 +208,19 @@ __device__ __forceinline__ double pair_dist(const float* X, long long i, const f
 }
 
 // Per cloud pair: the Chamfer sum (FP64) and the Hausdorff arg-maxes.
-// k_cd_partial: workgroup k of a pair reduces the points i = k*256 + t +
-// c*nblk*256 of P and j likewise of Q (a tree over the workgroup); then
-// k_cd_final adds the nblk partials in order.  The arg-maxes take the
-// largest float32 d2 with the smallest index.  Fixed order throughout.
+// k_cd_pick: a workgroup finds the nearest points of 256 points of P or of Q
+// and reduces them (a tree over the workgroup); k_cd_final reduces the
+// workgroups' partials, a thread's share in order and then a tree.  The
+// arg-maxes take the largest float32 d2 with the smallest index.  Fixed order
+// throughout.
 struct ChState {
     double cd;
     int istar, jstar;
 };
 struct ChPart {
     double cd;
-    float vi, vj;
-    int ii, jj;
+    float v;
+    int i;
 };
 
 __device__ __forceinline__ void argmax_merge(float& v, int& i, float v2, int i2) {
@@ -198,73 +230,101 @@ __device__ __forceinline__ void argmax_merge(float& v, int& i, float v2, int i2)
     }
 }
 
-template <int DIM>
-__global__ void __launch_bounds__(kWG) k_cd_partial(const float* __restrict__ P, int n, const float* __restrict__ Q,
-                                                   int m, const int* __restrict__ a, const float* __restrict__ da,
-                                                   const int* __restrict__ bq, const float* __restrict__ db,
-                                                   ChPart* __restrict__ part) {
-    __shared__ double sd[kWG];
-    __shared__ float svi[kWG], svj[kWG];
-    __shared__ int sii[kWG], sjj[kWG];
-    const int k = blockIdx.x, nblk = gridDim.x, b = blockIdx.y, t = threadIdx.x;
-    const float* Pb = P + (long long)b * n * DIM;
-    const float* Qb = Q + (long long)b * m * DIM;
-    const int* ab = a + (long long)b * n;
-    const int* bb = bq + (long long)b * m;
-    const float* dab = da + (long long)b * n;
-    const float* dbb = db + (long long)b * m;
-    float dir[3];
-    double acc = 0.0;
-    float vi = -1.f, vj = -1.f;
-    int ii = n, jj = m;
-    for (int i = k * kWG + t; i < n; i += nblk * kWG) {
-        acc += pair_dist<DIM>(Pb, i, Qb, ab[i], dir);
-        argmax_merge(vi, ii, dab[i], i);
-    }
-    for (int j = k * kWG + t; j < m; j += nblk * kWG) {
-        acc += pair_dist<DIM>(Pb, bb[j], Qb, j, dir);
-        argmax_merge(vj, jj, dbb[j], j);
-    }
-    sd[t] = acc;
-    svi[t] = vi;
-    sii[t] = ii;
-    svj[t] = vj;
-    sjj[t] = jj;
+// Tree over the workgroup of (sum, arg-max); thread 0 ends with the result.
+__device__ __forceinline__ void cd_tree(double& cd, float& v, int& i, double* sd, float* sv, int* si) {
+    const int t = threadIdx.x;
+    sd[t] = cd;
+    sv[t] = v;
+    si[t] = i;
     __syncthreads();
     for (int h = kWG / 2; h > 0; h >>= 1) {
         if (t < h) {
             sd[t] += sd[t + h];
-            argmax_merge(svi[t], sii[t], svi[t + h], sii[t + h]);
-            argmax_merge(svj[t], sjj[t], svj[t + h], sjj[t + h]);
+            argmax_merge(sv[t], si[t], sv[t + h], si[t + h]);
         }
         __syncthreads();
     }
-    if (t == 0) {
-        ChPart o;
-        o.cd = sd[0];
-        o.vi = svi[0];
-        o.ii = sii[0];
-        o.vj = svj[0];
-        o.jj = sjj[0];
-        part[(long long)b * nblk + k] = o;
-    }
+    cd = sd[0];
+    v = sv[0];
+    i = si[0];
+    __syncthreads();
 }
 
+// Fixed-point accumulation of the targets' pulls: each unit vector
+// component (|u| <= 1) is rounded to a multiple of 2^-40 and added as a
+// 64-bit integer.  Integer addition is exact and associative, so the sums
+// do not depend on the order the atomics land in (bitwise reproducible);
+// with at most 2^22 targets they stay below 2^62.
+constexpr double kFixScale = 1099511627776.0;  // 2^40
+
+// Grid (blocks of P, then blocks of Q; B).  part: [B][gridDim.x].
 template <int DIM>
-__global__ void k_cd_final(const float* __restrict__ P, int n, const float* __restrict__ Q, int m,
-                           const int* __restrict__ a, const int* __restrict__ bq, const ChPart* __restrict__ part,
-                           int nblk, int B, float* __restrict__ out, ChState* __restrict__ st) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= B) return;
-    const ChPart* pb = part + (long long)b * nblk;
+__global__ void __launch_bounds__(kWG) k_cd_pick(NnDir s0, NnDir s1, int blocks0, ChPart* __restrict__ part,
+                                                unsigned long long* __restrict__ acc) {
+    __shared__ double sd[kWG];
+    __shared__ float sv[kWG];
+    __shared__ int si[kWG];
+    const int b = blockIdx.y;
+    const bool second = (int)blockIdx.x >= blocks0;
+    const NnDir& s = second ? s1 : s0;
+    const int i = ((int)blockIdx.x - (second ? blocks0 : 0)) * kWG + (int)threadIdx.x;
+    double r = 0.0;
+    float v = -1.f;
+    int at = s.n;
+    if (i < s.n) {
+        const int j = nn_pick<DIM>(s, b, i, &v);
+        s.idx[(long long)b * s.n + i] = j;
+        at = i;
+        const float* Xb = s.X + (long long)b * s.n * DIM;
+        const float* Yb = s.Y + (long long)b * s.m * DIM;
+        double d[3], ss = 0.0;
+#pragma unroll
+        for (int x = 0; x < DIM; ++x) {
+            d[x] = (double)Xb[(long long)i * DIM + x] - (double)Yb[(long long)j * DIM + x];
+            ss += d[x] * d[x];
+        }
+        r = sqrt(ss);
+        if (second && acc && r != 0.0) {
+            // Q's point pulls its nearest point of P: the unit vector from Q to P
+            unsigned long long* o = acc + ((long long)b * s.m + j) * 3;
+#pragma unroll
+            for (int x = 0; x < DIM; ++x)
+                atomicAdd(o + x, (unsigned long long)__double2ll_rn(-d[x] / r * kFixScale));
+        }
+        if (!(v > -1.f)) {  // NaN: no candidate
+            v = -1.f;
+            at = s.n;
+        }
+    }
+    cd_tree(r, v, at, sd, sv, si);
+    if (threadIdx.x == 0) part[(long long)b * gridDim.x + blockIdx.x] = ChPart{r, v, at};
+}
+
+// One workgroup per cloud pair.
+template <int DIM>
+__global__ void __launch_bounds__(kWG) k_cd_final(const float* __restrict__ P, int n, const float* __restrict__ Q,
+                                                 int m, const int* __restrict__ a, const int* __restrict__ bq,
+                                                 const ChPart* __restrict__ part, int blocks0, int blocks1,
+                                                 float* __restrict__ out, ChState* __restrict__ st) {
+    __shared__ double sd[kWG];
+    __shared__ float sv[kWG];
+    __shared__ int si[kWG];
+    const int b = blockIdx.x, t = threadIdx.x;
+    const ChPart* pb = part + (long long)b * (blocks0 + blocks1);
     double cd = 0.0;
     float vi = -1.f, vj = -1.f;
     int ii = n, jj = m;
-    for (int k = 0; k < nblk; ++k) {
+    for (int k = t; k < blocks0 + blocks1; k += kWG) {
         cd += pb[k].cd;
-        argmax_merge(vi, ii, pb[k].vi, pb[k].ii);
-        argmax_merge(vj, jj, pb[k].vj, pb[k].jj);
+        if (k < blocks0) argmax_merge(vi, ii, pb[k].v, pb[k].i);
+        else argmax_merge(vj, jj, pb[k].v, pb[k].i);
     }
+    double none = 0.0;
+    cd_tree(cd, vi, ii, sd, sv, si);
+    cd_tree(none, vj, jj, sd, sv, si);
+    if (t != 0) return;
+    ii = min(ii, n - 1);  // only NaN distances: the last point stands for none
+    jj = min(jj, m - 1);
     const float* Pb = P + (long long)b * n * DIM;
     const float* Qb = Q + (long long)b * m * DIM;
     float dir[3];
@@ -275,37 +335,6 @@ __global__ void k_cd_final(const float* __restrict__ P, int n, const float* __re
     st[b].cd = cd;
     st[b].istar = ii;
     st[b].jstar = jj;
-}
-
-// Fixed-point accumulation of the targets' pulls: each unit vector
-// component (|u| <= 1) is rounded to a multiple of 2^-40 and added as a
-// 64-bit integer.  Integer addition is exact and associative, so the sums
-// do not depend on the order the atomics land in (bitwise reproducible);
-// with at most 2^22 targets they stay below 2^62.
-constexpr double kFixScale = 1099511627776.0;  // 2^40
-
-template <int DIM>
-__global__ void __launch_bounds__(kWG) k_cd_scatter(const float* __restrict__ P, int n, const float* __restrict__ Q,
-                                                   int m, const int* __restrict__ bq,
-                                                   unsigned long long* __restrict__ acc) {
-    const int b = blockIdx.y;
-    const int j = blockIdx.x * kWG + threadIdx.x;
-    if (j >= m) return;
-    const float* Pb = P + (long long)b * n * DIM;
-    const float* Qb = Q + (long long)b * m * DIM;
-    const int i = bq[(long long)b * m + j];
-    double d[3], s = 0.0;
-#pragma unroll
-    for (int x = 0; x < DIM; ++x) {
-        d[x] = (double)Pb[(long long)i * DIM + x] - (double)Qb[(long long)j * DIM + x];
-        s += d[x] * d[x];
-    }
-    const double r = sqrt(s);
-    if (r == 0.0) return;
-    unsigned long long* o = acc + ((long long)b * n + i) * 3;
-#pragma unroll
-    for (int x = 0; x < DIM; ++x)
-        atomicAdd(o + x, (unsigned long long)__double2ll_rn(d[x] / r * kFixScale));
 }
 
 // dCD/dP and dHD/dP, one thread per point of P.
@@ -360,68 +389,67 @@ __global__ void __launch_bounds__(kWG) k_cd_grad(const float* __restrict__ P, in
     }
 }
 
-template <int DIM>
-hipError_t nn_launch(hipStream_t st, int B, const float* X, int n, const float* Y, int m, const NnSplit& sp,
-                     int* idx, float* d2, int* pidx, float* pd2) {
-    const dim3 grid((unsigned)((n + kNnQueries - 1) / kNnQueries), (unsigned)sp.nranges, (unsigned)B);
-    if (sp.nranges == 1) {
-        hipLaunchKernelGGL((k_nn<DIM>), grid, dim3(kWG), 0, st, X, n, Y, m, sp.range, idx, d2, (long long)n);
-        return hipGetLastError();
-    }
-    const long long stride = (long long)sp.nranges * n;
-    hipLaunchKernelGGL((k_nn<DIM>), grid, dim3(kWG), 0, st, X, n, Y, m, sp.range, pidx, pd2, stride);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const long long items = (long long)B * n;
-    hipLaunchKernelGGL(k_nn_merge, dim3((unsigned)((items + kWG - 1) / kWG)), dim3(kWG), 0, st, pidx, pd2, n,
-                       sp.nranges, stride, B, idx, d2);
-    return hipGetLastError();
-}
-
-}  // namespace
-
-NnSplit nn_split(int B, int n, int m, int num_cus) {
-    NnSplit s;
-    const long long qblocks = (long long)B * ((n + kNnQueries - 1) / kNnQueries);
-    const long long want = 4ll * std::max(num_cus, 1);  // workgroups to fill the chip a few times over
-    const int max_ranges = std::max(1, (m + kNnTile - 1) / kNnTile);
-    long long r = qblocks >= want ? 1 : (want + qblocks - 1) / qblocks;
-    s.nranges = (int)std::min<long long>(r, max_ranges);
-    const int tiles = (m + kNnTile - 1) / kNnTile;
-    const int tiles_per = (tiles + s.nranges - 1) / s.nranges;
-    s.range = std::max(1, tiles_per) * kNnTile;
-    s.nranges = std::max(1, (m + s.range - 1) / s.range);
+NnDir nn_dir(const NnSplit& sp, const float* X, int n, const float* Y, int m, int* idx, float* d2, float* pd2,
+             int* pgrp) {
+    NnDir s;
+    s.X = X; s.Y = Y; s.n = n; s.m = m;
+    s.ql = sp.ql; s.qblocks = sp.qblocks; s.range = sp.range; s.nranges = sp.nranges;
+    s.pd2 = pd2; s.pgrp = pgrp; s.idx = idx; s.d2 = d2;
     return s;
 }
 
-hipError_t launch_nn(int dim, hipStream_t st, int B, const float* X, int n, const float* Y, int m,
-                     const NnSplit& sp, int* idx, float* d2, int* pidx, float* pd2) {
-    if (dim == 3) return nn_launch<3>(st, B, X, n, Y, m, sp, idx, d2, pidx, pd2);
-    if (dim == 2) return nn_launch<2>(st, B, X, n, Y, m, sp, idx, d2, pidx, pd2);
-    return hipErrorInvalidValue;
+int blocks_of(int n) { return (n + kWG - 1) / kWG; }
+
+}  // namespace
+
+// Queries per lane and target ranges of a search of n points among m: about
+// four workgroups per CU over the launch (`dirs` searches of B pairs).  Four
+// queries to a lane share each target read, so as many as leave ranges of 128
+// targets and more; small sets take one query per lane and ranges of 64.
+NnSplit nn_split(int B, int n, int m, int dirs, int num_cus) {
+    NnSplit s;
+    const long long want = std::max(1ll, 4ll * std::max(num_cus, 1) / dirs);
+    for (s.ql = 4;; s.ql /= 2) {
+        s.qblocks = (n + s.ql * kWG - 1) / (s.ql * kWG);
+        const long long r = (want + (long long)B * s.qblocks - 1) / ((long long)B * s.qblocks);
+        long long range = ((m + r - 1) / r + 63) / 64 * 64;
+        if (range > kNnTile) range = (range + kNnTile - 1) / kNnTile * kNnTile;
+        s.range = (int)range;
+        s.nranges = (int)((m + range - 1) / range);
+        if (s.ql == 1 || range >= 128) return s;
+    }
 }
 
-int cd_partials(int n, int m) { return std::max(1, std::min(256, (n + m + 2047) / 2048)); }
+hipError_t launch_nn(int dim, hipStream_t st, int B, const float* X, int n, const float* Y, int m,
+                     const NnSplit& sp, int* idx, float* d2, int* pgrp, float* pd2) {
+    const NnDir s = nn_dir(sp, X, n, Y, m, idx, d2, pd2, pgrp);
+    const dim3 grid((unsigned)(s.qblocks * s.nranges), (unsigned)B), pick((unsigned)blocks_of(n), (unsigned)B);
+#define ND_NN(D)                                                                                        \
+    hipLaunchKernelGGL((k_nn<D>), grid, dim3(kWG), 0, st, s, s, (unsigned long long*)nullptr, 0ll);     \
+    hipLaunchKernelGGL((k_nn_pick<D>), pick, dim3(kWG), 0, st, s);
+    if (dim == 3) { ND_NN(3) }
+    else if (dim == 2) { ND_NN(2) }
+    else return hipErrorInvalidValue;
+#undef ND_NN
+    return hipGetLastError();
+}
 
-hipError_t launch_cd(int dim, hipStream_t st, int B, const float* P, int n, const float* Q, int m, const int* a,
-                     const float* da, const int* bq, const float* db, float* out, void* state, void* part,
-                     void* acc, float* gcd, float* ghd) {
+hipError_t launch_cd(int dim, hipStream_t st, int B, const float* P, int n, const float* Q, int m, const NnSplit& sp,
+                     const NnSplit& sq, int* a, int* bq, int* pgrp_p, float* pd2_p, int* pgrp_q, float* pd2_q,
+                     float* out, void* state, void* part, void* acc, float* gcd, float* ghd) {
     ChState* cs = reinterpret_cast<ChState*>(state);
     ChPart* cp = reinterpret_cast<ChPart*>(part);
-    unsigned long long* ac = reinterpret_cast<unsigned long long*>(acc);
-    const int nblk = cd_partials(n, m);
-    const dim3 gp((unsigned)nblk, (unsigned)B), gf((unsigned)((B + kWG - 1) / kWG));
-    const dim3 gn((unsigned)((n + kWG - 1) / kWG), (unsigned)B), gm((unsigned)((m + kWG - 1) / kWG), (unsigned)B);
-    const bool grads = gcd || ghd;
-#define ND_CD(D)                                                                                               \
-    hipLaunchKernelGGL((k_cd_partial<D>), gp, dim3(kWG), 0, st, P, n, Q, m, a, da, bq, db, cp);                \
-    hipLaunchKernelGGL((k_cd_final<D>), gf, dim3(kWG), 0, st, P, n, Q, m, a, bq, cp, nblk, B, out, cs);        \
-    if (gcd) {                                                                                                 \
-        hipError_t z = launch_zero(st, reinterpret_cast<float*>(ac), (size_t)B * n * 3 * 2);                   \
-        if (z != hipSuccess) return z;                                                                         \
-        hipLaunchKernelGGL((k_cd_scatter<D>), gm, dim3(kWG), 0, st, P, n, Q, m, bq, ac);                       \
-    }                                                                                                          \
-    if (grads) hipLaunchKernelGGL((k_cd_grad<D>), gn, dim3(kWG), 0, st, P, n, Q, m, a, bq, cs, ac, gcd, ghd);
+    unsigned long long* ac = gcd ? reinterpret_cast<unsigned long long*>(acc) : nullptr;
+    const NnDir s0 = nn_dir(sp, P, n, Q, m, a, nullptr, pd2_p, pgrp_p);
+    const NnDir s1 = nn_dir(sq, Q, m, P, n, bq, nullptr, pd2_q, pgrp_q);
+    const dim3 gs((unsigned)(s0.qblocks * s0.nranges + s1.qblocks * s1.nranges), (unsigned)B);
+    const int b0 = blocks_of(n), b1 = blocks_of(m);
+    const dim3 gp((unsigned)(b0 + b1), (unsigned)B), gn((unsigned)b0, (unsigned)B);
+#define ND_CD(D)                                                                                                   \
+    hipLaunchKernelGGL((k_nn<D>), gs, dim3(kWG), 0, st, s0, s1, ac, ac ? (long long)B * n * 3 : 0ll);               \
+    hipLaunchKernelGGL((k_cd_pick<D>), gp, dim3(kWG), 0, st, s0, s1, b0, cp, ac);                                   \
+    hipLaunchKernelGGL((k_cd_final<D>), dim3((unsigned)B), dim3(kWG), 0, st, P, n, Q, m, a, bq, cp, b0, b1, out, cs); \
+    if (gcd || ghd) hipLaunchKernelGGL((k_cd_grad<D>), gn, dim3(kWG), 0, st, P, n, Q, m, a, bq, cs, ac, gcd, ghd);
     if (dim == 3) { ND_CD(3) }
     else if (dim == 2) { ND_CD(2) }
     else return hipErrorInvalidValue;
@@ -429,7 +457,7 @@ hipError_t launch_cd(int dim, hipStream_t st, int B, const float* P, int n, cons
     return hipGetLastError();
 }
 
-size_t cd_part_bytes(int n, int m) { return sizeof(ChPart) * (size_t)cd_partials(n, m); }
+size_t cd_part_bytes(int n, int m) { return sizeof(ChPart) * (size_t)(blocks_of(n) + blocks_of(m)); }
 
 size_t cd_state_bytes() { return sizeof(ChState); }
 

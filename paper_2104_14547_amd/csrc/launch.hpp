@@ -161,15 +161,17 @@ hipError_t launch_uv_bwd(const UvArgs& a, hipStream_t st, const float* gpts, uns
 
 // point-set losses (k_chamfer.hip)
 struct NnSplit {
-    int nranges;  // target ranges (workgroups along the target set)
-    int range;    // targets per range (a multiple of 256)
+    int ql, qblocks;  // query points per lane, workgroups along the query points
+    int nranges;      // target ranges (workgroups along the target set)
+    int range;        // targets per range (a multiple of 64)
 };
-NnSplit nn_split(int B, int n, int m, int num_cus);
+NnSplit nn_split(int B, int n, int m, int dirs, int num_cus);
 hipError_t launch_nn(int dim, hipStream_t st, int B, const float* X, int n, const float* Y, int m,
-                     const NnSplit& sp, int* idx, float* d2, int* pidx, float* pd2);
-hipError_t launch_cd(int dim, hipStream_t st, int B, const float* P, int n, const float* Q, int m, const int* a,
-                     const float* da, const int* bq, const float* db, float* out, void* state, void* part,
-                     void* acc, float* gcd, float* ghd);
+                     const NnSplit& sp, int* idx, float* d2, int* pgrp, float* pd2);
+// sp, sq: the searches of P's points among Q and of Q's among P
+hipError_t launch_cd(int dim, hipStream_t st, int B, const float* P, int n, const float* Q, int m, const NnSplit& sp,
+                     const NnSplit& sq, int* a, int* bq, int* pgrp_p, float* pd2_p, int* pgrp_q, float* pd2_q,
+                     float* out, void* state, void* part, void* acc, float* gcd, float* ghd);
 size_t cd_state_bytes();
 size_t cd_part_bytes(int n, int m);  // per pair
 
