@@ -18,15 +18,20 @@
 //
 // The order within a cell is the input's, so every sum has a fixed order and
 // results are bitwise reproducible, with no atomics on results and no pass to
-// find a fixed-point scale.  What bounds it: k_uv_cell's per-pair VALU work.
-// A bicubic pair costs 64 multiply-adds in FP64 for M, one per lane (lane o
-// owns output o and reads the wave's 64 pairs from LDS, two b128 reads per
-// four pairs), against 80 64-bit LDS atomics, as many conversions and a
-// second evaluation of every term on the atomic path.  Measured, backward
-// alone: 64 bicubic 16 x 16 surfaces x 65536 pairs 255 us (atomic path 600 us);
-// one surface of degree (4, 5), 48 x 41 net, 50001 pairs 122 us (1.70 ms, its
-// accumulators did not fit in LDS).  Largest error against 64 bits 1.6e-7 and
-// 2.3e-7 (5.8e-7 and 5.9e-7).
+// find a fixed-point scale.  What bounds it: k_uv_cell's per-pair VALU work
+// (span basis, the two contractions of the patch, the knot adjoints); the sums
+// M are on the matrix cores in FP64 (v_mfma_f64_4x4x4, 16 to a wave's 64
+// bicubic pairs), where the atomic path has 80 64-bit LDS atomics a pair, as
+// many conversions and a second evaluation of every term.  Measured, forward
+// and backward: 64 bicubic 16 x 16 surfaces x 65536 pairs 242 us (atomic path
+// 586 us), of them k_uv_cell 125, k_uv_order 34, k_uv_sum 19, k_uv_hist 16,
+// k_uv_scan 10, the forward 47; one surface of degree (4, 5), 48 x 41 net,
+// 50001 pairs 140 us (1.78 ms, its accumulators did not fit in LDS).  With M
+// summed on the VALU (one output per lane) k_uv_cell took 138 us, without the
+// next pairs' loads in flight 144; k_uv_sum 37 us with one thread to a control
+// point's value; k_uv_hist and k_uv_scan 18 and 13 us with 128 chunks to a
+// surface instead of 64.  Largest error against 64 bits 2.3e-7 and 1.6e-7
+// (5.9e-7 and 6.8e-7).
 #include "device.hpp"
 #include "launch.hpp"
 #include "../../include/nurbsdiff.h"
@@ -105,7 +110,7 @@ __global__ void __launch_bounds__(kScanWG) k_uv_scan(UvSort s, SortPtrs t) {
     for (int c = tid; c < kUvCellsMax; c += kScanWG) {
         unsigned run = 0;
         if (c < s.cells) {
-            constexpr int kU = 8;
+            constexpr int kU = 32;  // chunks in flight
             for (int j0 = 0; j0 < s.nchunk; j0 += kU) {
                 unsigned v[kU];
 #pragma unroll
@@ -179,21 +184,31 @@ __global__ void __launch_bounds__(kWave) k_uv_order(UvArgs a, UvSort s, SortPtrs
     const unsigned short* cell = t.cell + (size_t)g * a.npts;
     unsigned* order = t.order + (size_t)g * a.npts;
     const int k0 = blockIdx.x * s.chunk, k1 = min(a.npts, k0 + s.chunk);
-    for (int k = k0; k < k1; k += kWave) {
-        const bool act = k + lane < k1;
-        const int c = act ? (int)cell[k + lane] : 0;
-        unsigned long long m = __ballot(act);
-        for (int i = 0; i < bits; ++i) {
-            const bool bit = (c >> i) & 1;
-            const unsigned long long v = __ballot(bit);
-            m &= bit ? v : ~v;
+    // eight rows of 64 pairs fetched together
+    constexpr int kU = 8;
+    for (int kk = k0; kk < k1; kk += kU * kWave) {
+        int cs8[kU];
+#pragma unroll
+        for (int i = 0; i < kU; ++i) cs8[i] = (int)cell[min(kk + i * kWave + lane, k1 - 1)];
+#pragma unroll
+        for (int row = 0; row < kU; ++row) {
+            const int k = kk + row * kWave;
+            if (k >= k1) break;
+            const bool act = k + lane < k1;
+            const int c = act ? cs8[row] : 0;
+            unsigned long long m = __ballot(act);
+            for (int i = 0; i < bits; ++i) {
+                const bool bit = (c >> i) & 1;
+                const unsigned long long v = __ballot(bit);
+                m &= bit ? v : ~v;
+            }
+            const int rank = __popcll(m & ((1ull << lane) - 1ull));
+            const unsigned base = next[c];
+            wave_lds_sync();
+            if (act && rank == 0) next[c] = base + (unsigned)__popcll(m);
+            wave_lds_sync();
+            if (act) order[base + rank] = (unsigned)(k + lane);
         }
-        const int rank = __popcll(m & ((1ull << lane) - 1ull));
-        const unsigned base = next[c];
-        wave_lds_sync();
-        if (act && rank == 0) next[c] = base + (unsigned)__popcll(m);
-        wave_lds_sync();
-        if (act) order[base + rank] = (unsigned)(k + lane);
     }
 }
 
@@ -326,29 +341,39 @@ __global__ void __launch_bounds__(kWG) k_uv_cell(UvArgs a, UvSort s, SortPtrs t,
     const float* gb = gpts + (size_t)b * a.npts * 3;
     const unsigned* order = t.order + (size_t)g * a.npts;
 
-    // outputs o = (r (q+1) + h) 4 + c owned by this lane
-    constexpr int kOwn = ((PM + 1) * (QM + 1) * 4 + kWave - 1) / kWave;
-    double acc[kOwn];
-    int row_u[kOwn], row_v[kOwn];
+    // M_rh of value c on the matrix cores (v_mfma_f64_4x4x4: four blocks, one per
+    // h, of 4 rows r x 4 values c, over 4 pairs): lane l holds row r = l / 16 and
+    // column (h, c) = l % 16 of the result, and hands in pair quarter l / 16 of
+    // row r = l % 4 and of column l % 16.  Degrees above 3 take more tiles.
+    constexpr int kRT = (PM + 4) / 4, kHT = (QM + 4) / 4;
+    double acc[kRT][kHT];
 #pragma unroll
-    for (int m = 0; m < kOwn; ++m) {
-        const int o = min(lane + m * kWave, 4 * npatch - 1), rh = o >> 2;
-        row_u[m] = rh / (q + 1);
-        row_v[m] = (rh - row_u[m] * (q + 1)) * 4 + (o & 3);
-        acc[m] = 0.0;
-    }
+    for (int i = 0; i < kRT; ++i)
+#pragma unroll
+        for (int j = 0; j < kHT; ++j) acc[i][j] = 0.0;
     double sku[2 * PM], skv[2 * QM];
 #pragma unroll
     for (int i = 0; i < 2 * PM; ++i) sku[i] = 0.0;
 #pragma unroll
     for (int i = 0; i < 2 * QM; ++i) skv[i] = 0.0;
 
+    // the next 64 pairs' values and the index of the 64 after them are on the
+    // way while the current ones are worked on
+    size_t id = order[min(s0 + lane, s1 - 1)];
+    float2 nx = *reinterpret_cast<const float2*>(uvb + 2 * id);
+    float3u ng = *reinterpret_cast<const float3u*>(gb + 3 * id);
+    id = order[min(s0 + kWave + lane, s1 - 1)];
     for (int k = s0; k < s1; k += kWave) {
         const bool act = k + lane < s1;
-        const size_t id = order[min(k + lane, s1 - 1)];
-        const float2 x = *reinterpret_cast<const float2*>(uvb + 2 * id);
+        const float2 x = nx;
+        const float3u gv = ng;
+        if (k + kWave < s1) {
+            nx = *reinterpret_cast<const float2*>(uvb + 2 * id);
+            ng = *reinterpret_cast<const float3u*>(gb + 3 * id);
+            id = order[min(k + 2 * kWave + lane, s1 - 1)];
+        }
         const float u = fminf(fmaxf(x.x, ulo), uhi), v = fminf(fmaxf(x.y, vlo), vhi);
-        const float g0 = act ? gb[3 * id] : 0.f, g1 = act ? gb[3 * id + 1] : 0.f, g2 = act ? gb[3 * id + 2] : 0.f;
+        const float g0 = act ? gv.x : 0.f, g1 = act ? gv.y : 0.f, g2 = act ? gv.z : 0.f;
         float Nu[PM + 1], Nv[QM + 1], su[PM * (PM + 1) / 2], sv[QM * (QM + 1) / 2];
         span_basis_rt<PM>(tu, p, u, Nu, su);
         span_basis_rt<QM>(tv, q, v, Nv, sv);
@@ -406,19 +431,29 @@ __global__ void __launch_bounds__(kWG) k_uv_cell(UvArgs a, UvSort s, SortPtrs t,
             for (int i = 0; i < 2 * QM; ++i) skv[i] += (double)gk[i];
         }
         if (want_pw) {
-            // pairs past the item's end hold h = 0
-            const int n4 = (min(kWave, s1 - k) + 3) >> 2;
-#pragma unroll 2
-            for (int j = 0; j < n4; ++j) {
+            // pairs past the item's end hold h = 0; rows past the degree hold 0
+            // too, or reach only values that are not kept
+            const int quarter = lane >> 4;
 #pragma unroll
-                for (int m = 0; m < kOwn; ++m) {
-                    const float4 x4 = *reinterpret_cast<const float4*>(&L.nu[row_u[m]][4 * j]);
-                    const float4 y4 = *reinterpret_cast<const float4*>(&L.tv[row_v[m]][4 * j]);
-                    acc[m] = __builtin_fma((double)x4.x, (double)y4.x, acc[m]);
-                    acc[m] = __builtin_fma((double)x4.y, (double)y4.y, acc[m]);
-                    acc[m] = __builtin_fma((double)x4.z, (double)y4.z, acc[m]);
-                    acc[m] = __builtin_fma((double)x4.w, (double)y4.w, acc[m]);
-                }
+            for (int j = 0; j < 4; ++j) {
+                float4 x4[kRT], y4[kHT];
+#pragma unroll
+                for (int i = 0; i < kRT; ++i)
+                    x4[i] = *reinterpret_cast<const float4*>(&L.nu[min(4 * i + (lane & 3), PM)][16 * quarter + 4 * j]);
+#pragma unroll
+                for (int i = 0; i < kHT; ++i)
+                    y4[i] = *reinterpret_cast<const float4*>(
+                        &L.tv[min(16 * i + (lane & 15), 4 * QM + 3)][16 * quarter + 4 * j]);
+#pragma unroll
+                for (int i = 0; i < kRT; ++i)
+#pragma unroll
+                    for (int h = 0; h < kHT; ++h) {
+                        if (4 * i > p || 4 * h > q) continue;
+                        acc[i][h] = __builtin_amdgcn_mfma_f64_4x4x4f64(x4[i].x, y4[h].x, acc[i][h], 0, 0, 0);
+                        acc[i][h] = __builtin_amdgcn_mfma_f64_4x4x4f64(x4[i].y, y4[h].y, acc[i][h], 0, 0, 0);
+                        acc[i][h] = __builtin_amdgcn_mfma_f64_4x4x4f64(x4[i].z, y4[h].z, acc[i][h], 0, 0, 0);
+                        acc[i][h] = __builtin_amdgcn_mfma_f64_4x4x4f64(x4[i].w, y4[h].w, acc[i][h], 0, 0, 0);
+                    }
             }
         }
     }
@@ -426,15 +461,20 @@ __global__ void __launch_bounds__(kWG) k_uv_cell(UvArgs a, UvSort s, SortPtrs t,
     double* out = t.slots + ((size_t)g * s.items + item) * s.slot;
     if (want_pw) {
 #pragma unroll
-        for (int m = 0; m < kOwn; ++m) {
-            // M_x, M_y, M_z, M_w of one control point sit in four neighbouring lanes
-            const int l0 = lane & ~3, o = lane + m * kWave;
-            const double mx = __shfl(acc[m], l0), my = __shfl(acc[m], l0 + 1), mz = __shfl(acc[m], l0 + 2);
-            const int src = min(o >> 2, npatch - 1);
-            const float px = __shfl(pc.x, src), py = __shfl(pc.y, src), pz = __shfl(pc.z, src), w = __shfl(pc.w, src);
-            const double dw = (double)px * mx + (double)py * my + (double)pz * mz + acc[m];
-            if (o < 4 * npatch) out[o] = (o & 3) == 3 ? dw : (double)w * acc[m];
-        }
+        for (int i = 0; i < kRT; ++i)
+#pragma unroll
+            for (int j = 0; j < kHT; ++j) {
+                // M_x, M_y, M_z, M_w of one control point sit in four neighbouring lanes
+                const double M = acc[i][j];
+                const int l0 = lane & ~3, r = 4 * i + (lane >> 4), h = 4 * j + ((lane >> 2) & 3);
+                const double mx = __shfl(M, l0), my = __shfl(M, l0 + 1), mz = __shfl(M, l0 + 2);
+                const bool kept = r <= p && h <= q;
+                const int src = kept ? r * (q + 1) + h : 0;
+                const float px = __shfl(pc.x, src), py = __shfl(pc.y, src), pz = __shfl(pc.z, src),
+                            w = __shfl(pc.w, src);
+                const double dw = (double)px * mx + (double)py * my + (double)pz * mz + M;
+                if (kept) out[4 * src + (lane & 3)] = (lane & 3) == 3 ? dw : (double)w * M;
+            }
     }
     double* buf = reinterpret_cast<double*>(&L.nu[0][0]);
     if (want_ku) {
@@ -458,24 +498,34 @@ __device__ __forceinline__ double cell_sum(const int* __restrict__ is, const dou
     return x;
 }
 
-// Grid (blocks, surfaces).  The first cblk workgroups: one thread per value
-// of a control point; the others: one wave per knot, its lanes over the cells.
-__global__ void __launch_bounds__(kWG) k_uv_sum(UvArgs a, UvSort s, SortPtrs t, int b0, int cblk, unsigned mask,
-                                               float* __restrict__ gc, float* __restrict__ gw,
+// Grid (blocks, surfaces).  The first cblk workgroups: 4 values x 2^rbits
+// (>= p + 1) rows of cells to a control point; the others: one wave per knot, its lanes over the cells.
+__global__ void __launch_bounds__(kWG) k_uv_sum(UvArgs a, UvSort s, SortPtrs t, int b0, int cblk, int rbits,
+                                               unsigned mask, float* __restrict__ gc, float* __restrict__ gw,
                                                float* __restrict__ gku, float* __restrict__ gkv) {
     const int g = blockIdx.y, b = b0 + g, p = a.p, q = a.q;
     const int ncu = a.nu_c - p, ncv = s.ncv;
     const int* is = t.item_start + (size_t)g * (s.cells + 1);
     const double* slots = t.slots + (size_t)g * s.items * s.slot;
     if ((int)blockIdx.x < cblk) {
-        const int e = blockIdx.x * kWG + threadIdx.x, ij = e >> 2, c = e & 3;
-        const int ncp = a.nu_c * a.nv_c;
-        if (ij >= ncp || !(mask & (c == 3 ? NURBS_GRAD_W : NURBS_GRAD_CTRL))) return;
-        const int i = ij / a.nv_c, j = ij - i * a.nv_c;
+        // lanes: value c (4), then row r of the control point's cells (a power
+        // of two of them); rows are added in a fixed tree
+        const int lanes = 4 << rbits;
+        const int e = (int)blockIdx.x * (kWG / lanes) + (int)threadIdx.x / lanes;
+        const int c = threadIdx.x & 3, r = (threadIdx.x >> 2) & ((1 << rbits) - 1);
+        const int ncp = a.nu_c * a.nv_c, ij = min(e, ncp - 1);
+        const int i = ij / a.nv_c, j = ij - i * a.nv_c, cu = i - r;
         double x = 0.0;
-        for (int cu = max(0, i - p); cu <= min(i, ncu - 1); ++cu)
-            for (int cv = max(0, j - q); cv <= min(j, ncv - 1); ++cv)
-                x += cell_sum(is, slots, s.slot, cu * ncv + cv, 4 * ((i - cu) * (q + 1) + j - cv) + c);
+        if (r <= p && cu >= 0 && cu < ncu) {
+            const int v0 = max(0, j - q), v1 = min(j, ncv - 1), o = 4 * (r * (q + 1) + j) + c;
+            int at = is[cu * ncv + v0];
+            for (int cv = v0; cv <= v1; ++cv) {
+                const int end = is[cu * ncv + cv + 1];
+                for (; at < end; ++at) x += slots[(size_t)at * s.slot + o - 4 * cv];
+            }
+        }
+        for (int d = 4; d < lanes; d <<= 1) x += __shfl_xor(x, d);
+        if (e >= ncp || r != 0 || !(mask & (c == 3 ? NURBS_GRAD_W : NURBS_GRAD_CTRL))) return;
         if (c < 3) gc[3 * ((size_t)b * ncp + ij) + c] = (float)x;
         else gw[(size_t)b * ncp + ij] = (float)x;
         return;
@@ -523,7 +573,7 @@ bool uv_sort_plan(int B, int p, int q, int nu_c, int nv_c, int npts, size_t head
     s.cells = (int)cells;
     // nothing that fixes the order of a sum depends on B, so that a surface's
     // result does not depend on the batch it is in
-    const long long c = ((long long)npts + 127) / 128;
+    const long long c = ((long long)npts + 63) / 64;
     s.chunk = (int)std::max<long long>(256, (c + kWave - 1) / kWave * kWave);
     s.nchunk = (npts + s.chunk - 1) / s.chunk;
     s.seg = npts >= 32768 ? 512 : 128;
@@ -560,7 +610,9 @@ hipError_t launch_uv_bwd_sorted(const UvArgs& a, const UvSort& s, char* ws, hipS
     int bits = 0;
     while ((1 << bits) < s.cells) ++bits;
     const size_t lds = sizeof(unsigned) * (size_t)s.cells;
-    const int cblk = (4 * a.nu_c * a.nv_c + kWG - 1) / kWG;
+    int rbits = 0;
+    while ((1 << rbits) < a.p + 1) ++rbits;
+    const int cblk = ((4 << rbits) * a.nu_c * a.nv_c + kWG - 1) / kWG;
     const int kblk = (a.nu_c + a.p + 1 + a.nv_c + a.q + 1 + kWavesPerWG - 1) / kWavesPerWG;
     for (int b0 = 0; b0 < a.B; b0 += s.group) {
         const unsigned nb = (unsigned)std::min(s.group, a.B - b0);
@@ -572,8 +624,8 @@ hipError_t launch_uv_bwd_sorted(const UvArgs& a, const UvSort& s, char* ws, hipS
         if (m <= 3) launch_cell<3, 3>(gi, st, a, s, t, b0, gpts, mask);
         else if (m <= 5) launch_cell<5, 5>(gi, st, a, s, t, b0, gpts, mask);
         else launch_cell<7, 7>(gi, st, a, s, t, b0, gpts, mask);
-        hipLaunchKernelGGL(k_uv_sum, dim3((unsigned)(cblk + kblk), nb), dim3(kWG), 0, st, a, s, t, b0, cblk, mask, gc,
-                           gw, gku, gkv);
+        hipLaunchKernelGGL(k_uv_sum, dim3((unsigned)(cblk + kblk), nb), dim3(kWG), 0, st, a, s, t, b0, cblk, rbits, mask,
+                           gc, gw, gku, gkv);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
