@@ -96,7 +96,7 @@ extern "C" {
 #define NURBS_PLAN_WS_HEADER 4352
 
 /* tile schedules of the ragged-batch plans (nurbs_ctx_set_schedule) */
-#define NURBS_SCHED_STATIC 0  /* tiles assigned to waves when the plan is built (default) */
+#define NURBS_SCHED_STATIC 0  /* a wave per tile, in an order fixed when the plan is built (default) */
 #define NURBS_SCHED_DYNAMIC 1 /* waves take tiles from counters at run time */
 
 typedef struct nurbs_ctx nurbs_ctx;
@@ -136,12 +136,11 @@ int nurbs_ctx_set_knot_sigma(nurbs_ctx *ctx, float sigma);
  * change the summation order of the backward within the tolerances.  An
  * autotuner picks these per workload. */
 int nurbs_ctx_set_tiling(nurbs_ctx *ctx, int fwd_tile_points, int bwd_tile_points);
-/* How plans created later on this context hand tiles to their persistent
- * waves (Alg. Forward / Alg. Backward run all tiles in parallel; this is
- * only their order on the GPU):
- *   NURBS_SCHED_STATIC  : each wave runs a list fixed when the plan is built
- *                         (longest-processing-time greedy on a cost model);
- *                         the default;
+/* How plans created later on this context hand tiles to waves (Alg. Forward
+ * / Alg. Backward run all tiles in parallel; this is only their order on the
+ * GPU):
+ *   NURBS_SCHED_STATIC  : a wave per tile, by decreasing estimated cost, as
+ *                         CUs become free; the default;
  *   NURBS_SCHED_DYNAMIC : the tiles are ordered by decreasing estimated cost
  *                         and dealt to 16 queues; each wave runs one tile of
  *                         its queue and then takes the next from the queue's
@@ -395,7 +394,7 @@ int nurbs_chamfer(nurbs_ctx *ctx, int B, int dim, const float *P, int n, const f
 
 /* ------------------------------------------------------------------------
  * Ragged batch ("plan"): thousands of surfaces of uneven degree, control
- * grid and sample grid in one persistent launch per direction (the paper's
+ * grid and sample grid in one launch per direction (the paper's
  * batched forward of Alg. Forward over all surfaces, and Alg. Backward).
  *   host     : n descriptors in host memory (copied; may be freed after).
  *   flags    : NURBS_VALIDATE or 0.
@@ -404,8 +403,8 @@ int nurbs_chamfer(nurbs_ctx *ctx, int B, int dim, const float *P, int n, const f
  * The plan is bound to the device current at creation.  nurbs_plan_fwd /
  * nurbs_plan_bwd take packed arrays laid out as the descriptors say, launch
  * without host synchronisation or allocation, and may be captured in a HIP
- * graph.  Tiles are assigned to the persistent waves when the plan is built
- * (no device-side work queue), so calls of one plan on different streams may
+ * graph.  The order of the tiles is fixed when the plan is built (no
+ * device-side work queue), so calls of one plan on different streams may
  * overlap as long as each has its own workspace and outputs; the host-side
  * calls themselves are not thread-safe (one thread per plan).
  * ---------------------------------------------------------------------- */

@@ -642,7 +642,7 @@ def hausdorff_loss(P, Q):
 
 class SurfaceBatch:
     """A ragged batch plan (nurbs_plan_*): surfaces of uneven degree, control
-    grid and sample grid, one persistent launch per direction.
+    grid and sample grid, one launch per direction.
 
     ``shapes`` int [n][6] = (p, q, nu_c, nv_c, nu_s, nv_s); ``offsets`` int
     [n][7] element offsets of (ctrl, w, ku, kv, us, vs, pts) in the packed

@@ -9,7 +9,6 @@
 #include <cstring>
 #include <mutex>
 #include <numeric>
-#include <queue>
 #include <string>
 #include <vector>
 
@@ -44,8 +43,6 @@ struct nurbs_plan {
     DevTile* d_btiles = nullptr;
     ExecTile* d_bexec = nullptr;  // backward execution records, wave order
     ExecTile* d_gexec = nullptr;  // backward records by decreasing estimated gather work
-    int* d_fbegin = nullptr;      // wave boundaries in d_fexec
-    int* d_bbegin = nullptr;      // wave boundaries in d_bexec
     int2* d_fin = nullptr;        // finalize parts (surface, part), most expensive first
     int nfin = 0;
     int nf = 0, nb = 0;
@@ -63,7 +60,7 @@ struct nurbs_plan {
 
 // byte offsets of the device tables inside one allocation
 struct PlanLayout {
-    size_t desc, ftiles, fexec, btiles, bexec, gexec, fbegin, bbegin, fin, total;
+    size_t desc, ftiles, fexec, btiles, bexec, gexec, fin, total;
 };
 
 namespace {
@@ -969,43 +966,11 @@ std::vector<int> longest_first(const std::vector<double>& cost) {
     return idx;
 }
 
-// Static schedule: assign tiles to nw waves, longest first, each to the wave
-// with the least work so far.  Returns the tiles in wave order and the wave
-// boundaries.  Dynamic schedule: the longest-first order itself (the waves
-// take tiles from it at run time); the boundaries are unused.
-void assign_waves(const std::vector<double>& cost, int nw, std::vector<int>& order, std::vector<int>& begin,
-                  bool dynamic) {
-    std::vector<int> idx = longest_first(cost);
-    if (dynamic) {
-        order = idx;
-        begin.assign(nw + 1, 0);
-        return;
-    }
-    using Load = std::pair<double, int>;
-    std::priority_queue<Load, std::vector<Load>, std::greater<Load>> heap;
-    for (int w = 0; w < nw; ++w) heap.push({0.0, w});
-    std::vector<std::vector<int>> lists(nw);
-    for (int t : idx) {
-        Load l = heap.top();
-        heap.pop();
-        lists[l.second].push_back(t);
-        l.first += cost[t];
-        heap.push(l);
-    }
-    order.clear();
-    begin.assign(nw + 1, 0);
-    for (int w = 0; w < nw; ++w) {
-        begin[w] = (int)order.size();
-        order.insert(order.end(), lists[w].begin(), lists[w].end());
-    }
-    begin[nw] = (int)order.size();
-}
-
 }  // namespace
 
 namespace {
-// Host half of plan creation: validate the descriptors, cut tiles, assign
-// them to waves and lay out the device tables in *blob.  The device pointers
+// Host half of plan creation: validate the descriptors, cut tiles, order
+// them and lay out the device tables in *blob.  The device pointers
 // are bound by plan_bind once the blob has a device address.  With blob ==
 // NULL only the sizes (layout, workspace) are worked out.
 int plan_build(nurbs_ctx* ctx, const nurbs_desc* host, int n, unsigned flags, nurbs_plan** out,
@@ -1081,7 +1046,12 @@ int plan_build(nurbs_ctx* ctx, const nurbs_desc* host, int n, unsigned flags, nu
     pl->nb = (int)bt.size();
     pl->ws_bytes = kPlanHeader + slot_off;
 
-    // degree class and persistent grid: as many workgroups as fit at once
+    // degree class and grid.  Static schedule: a wave per tile, longest first,
+    // so the hardware hands the next tiles to whichever CU is free; for 4096
+    // uneven surfaces (14033 forward, 10978 backward tiles) the forward took
+    // 118 us and the row loop 231, with a list per resident wave fixed here
+    // (longest-processing-time greedy on the same costs) 122 and 249.  Dynamic:
+    // as many workgroups as fit at once, which draw tiles at run time.
     int maxdeg = 1;
     for (const auto& d : pl->host) maxdeg = std::max(maxdeg, std::max(d.p, d.q));
     pl->maxd = maxdeg <= 5 ? 5 : 7;
@@ -1095,9 +1065,13 @@ int plan_build(nurbs_ctx* ctx, const nurbs_desc* host, int n, unsigned flags, nu
             return hip_fail(ctx, e, "hipOccupancyMaxActiveBlocksPerMultiprocessor");
         }
     }
-    const int occ_f = std::max(occ[0], 1), occ_b = std::max(occ[1], 1);
-    pl->grid_fwd = std::max(1, std::min(occ_f * cus, (pl->nf + kWavesPerWG - 1) / kWavesPerWG));
-    pl->grid_bwd = std::max(1, std::min(occ_b * cus, (pl->nb + kWavesPerWG - 1) / kWavesPerWG));
+    const bool dynamic = pl->schedule == NURBS_SCHED_DYNAMIC;
+    auto grid_of = [&](int tiles, int blocks_per_cu) {
+        const int all = std::max(1, (tiles + kWavesPerWG - 1) / kWavesPerWG);
+        return dynamic ? std::min(all, std::max(blocks_per_cu, 1) * cus) : all;
+    };
+    pl->grid_fwd = grid_of(pl->nf, occ[0]);
+    pl->grid_bwd = grid_of(pl->nb, occ[1]);
     // finalize parts, most expensive first (estimated dependent memory rounds)
     std::vector<int2> fin;
     std::vector<double> fin_cost;
@@ -1126,7 +1100,6 @@ int plan_build(nurbs_ctx* ctx, const nurbs_desc* host, int n, unsigned flags, nu
     pl->nfin = (int)fin.size();
 
     // table layout (sizes follow from the counts alone)
-    const size_t nwf = (size_t)pl->grid_fwd * kWavesPerWG, nwb = (size_t)pl->grid_bwd * kWavesPerWG;
     auto al = [](size_t x) { return (x + 255) & ~size_t(255); };
     const size_t o_desc = 0;
     const size_t o_ft = o_desc + al(sizeof(DevDesc) * std::max(n, 1));
@@ -1134,18 +1107,14 @@ int plan_build(nurbs_ctx* ctx, const nurbs_desc* host, int n, unsigned flags, nu
     const size_t o_bt = o_fx + al(sizeof(ExecTile) * std::max<size_t>(ft.size(), 1));
     const size_t o_bx = o_bt + al(sizeof(DevTile) * std::max<size_t>(bt.size(), 1));
     const size_t o_gx = o_bx + al(sizeof(ExecTile) * std::max<size_t>(bt.size(), 1));
-    const size_t o_fb = o_gx + al(sizeof(ExecTile) * std::max<size_t>(bt.size(), 1));
-    const size_t o_bb = o_fb + al(sizeof(int) * (nwf + 1));
-    const size_t o_fi = o_bb + al(sizeof(int) * (nwb + 1));
+    const size_t o_fi = o_gx + al(sizeof(ExecTile) * std::max<size_t>(bt.size(), 1));
     const size_t total = o_fi + al(sizeof(int2) * std::max<size_t>(fin.size(), 1));
     if (!blob) {  // size query: no schedule, no tables
-        *lay = PlanLayout{o_desc, o_ft, o_fx, o_bt, o_bx, o_gx, o_fb, o_bb, o_fi, total};
+        *lay = PlanLayout{o_desc, o_ft, o_fx, o_bt, o_bx, o_gx, o_fi, total};
         *out = pl;
         return NURBS_OK;
     }
-    std::vector<int> fo, fbeg, bo, bbeg;
-    assign_waves(fcost, (int)nwf, fo, fbeg, pl->schedule == NURBS_SCHED_DYNAMIC);
-    assign_waves(bcost, (int)nwb, bo, bbeg, pl->schedule == NURBS_SCHED_DYNAMIC);
+    const std::vector<int> fo = longest_first(fcost), bo = longest_first(bcost);
     auto record = [&](const DevTile& t) {
         const DevDesc& x = dd[t.surf];
         ExecTile r;
@@ -1170,10 +1139,8 @@ int plan_build(nurbs_ctx* ctx, const nurbs_desc* host, int n, unsigned flags, nu
     if (!bt.empty()) memcpy(hb + o_bt, bt.data(), sizeof(DevTile) * bt.size());
     if (!bx.empty()) memcpy(hb + o_bx, bx.data(), sizeof(ExecTile) * bx.size());
     if (!gx.empty()) memcpy(hb + o_gx, gx.data(), sizeof(ExecTile) * gx.size());
-    memcpy(hb + o_fb, fbeg.data(), sizeof(int) * fbeg.size());
-    memcpy(hb + o_bb, bbeg.data(), sizeof(int) * bbeg.size());
     if (!fin.empty()) memcpy(hb + o_fi, fin.data(), sizeof(int2) * fin.size());
-    *lay = PlanLayout{o_desc, o_ft, o_fx, o_bt, o_bx, o_gx, o_fb, o_bb, o_fi, total};
+    *lay = PlanLayout{o_desc, o_ft, o_fx, o_bt, o_bx, o_gx, o_fi, total};
     *out = pl;
     return NURBS_OK;
 }
@@ -1186,8 +1153,6 @@ void plan_bind(nurbs_plan* pl, void* dev, const PlanLayout& lay) {
     pl->d_btiles = reinterpret_cast<DevTile*>(base + lay.btiles);
     pl->d_bexec = reinterpret_cast<ExecTile*>(base + lay.bexec);
     pl->d_gexec = reinterpret_cast<ExecTile*>(base + lay.gexec);
-    pl->d_fbegin = reinterpret_cast<int*>(base + lay.fbegin);
-    pl->d_bbegin = reinterpret_cast<int*>(base + lay.bbegin);
     pl->d_fin = reinterpret_cast<int2*>(base + lay.fin);
 }
 }  // namespace
@@ -1280,7 +1245,6 @@ PlanArgs plan_args(nurbs_plan* pl, bool bwd, void* ws, const float* ctrl, const 
     a.exec = bwd ? pl->d_bexec : pl->d_fexec;
     a.gexec = bwd ? pl->d_gexec : nullptr;
     a.ntiles = bwd ? pl->nb : pl->nf;
-    a.wave_begin = bwd ? pl->d_bbegin : pl->d_fbegin;
     a.nwaves = (bwd ? pl->grid_bwd : pl->grid_fwd) * kWavesPerWG;
     // dynamic schedule: the tile counters live in the workspace header
     a.queue = pl->schedule == NURBS_SCHED_DYNAMIC ? reinterpret_cast<int*>(reinterpret_cast<char*>(ws) +

@@ -61,12 +61,11 @@ static_assert(sizeof(ExecTile) == 104, "ExecTile layout");
 struct PlanArgs {
     const DevDesc* desc;
     const DevTile* tiles;     // natural order (finalize)
-    const ExecTile* exec;     // execution records; wave w runs exec[wave_begin[w] .. wave_begin[w + 1])
+    const ExecTile* exec;     // execution records by decreasing estimated cost; static schedule: wave w runs exec[w]
     const ExecTile* gexec;    // backward: the same records by decreasing estimated gather work
-    const int* wave_begin;    // [nwaves + 1], assigned at plan creation (static schedule)
     int* queue;               // dynamic schedule: kQueues tile counters (zeroed before the launch); NULL: static
     int ntiles;
-    int nwaves;               // persistent waves in the grid (grid * kWavesPerWG)
+    int nwaves;               // waves in the grid (grid * kWavesPerWG)
     unsigned flags;
     int* err;
     const float *ctrl, *w, *ku, *kv, *us, *vs;
@@ -95,7 +94,7 @@ ND_DECLARE_UNIFORM(6)
 ND_DECLARE_UNIFORM(7)
 #undef ND_DECLARE_UNIFORM
 
-// ragged batch: persistent kernels for degree class <= 5 and <= 7
+// ragged batch: kernels for degree class <= 5 and <= 7
 #define ND_DECLARE_PLAN(M)                                                                            \
     hipError_t launch_plan_fwd_d##M(dim3 grid, hipStream_t st, const PlanArgs& a, float* pts);        \
     hipError_t launch_plan_bwd_d##M(dim3 grid, hipStream_t st, const PlanArgs& a, const float* gpts,  \
