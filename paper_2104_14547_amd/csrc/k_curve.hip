@@ -332,7 +332,7 @@ __device__ __forceinline__ int curve_items(const CurveLds& l, int spans, int n, 
         const int c = c0 + (int)threadIdx.x;
         used += __syncthreads_count(c < spans && l.first[c + 1] > l.first[c]);
     }
-    const int room = kT * ((used + kWave - 1) / kWave);
+    const int room = kT * (used / kWave + 1);  // more than the spans used, so both lengths exist
     int len = (2 * n + 2 * room - used - 1) / (2 * room - used);  // half an item lost per span
     auto count = [&](int c) { return (l.first[c + 1] - l.first[c] + len - 1) / len; };
     *nitems = span_prefix<W>(l, spans, l.item, count);

@@ -23,6 +23,15 @@ def test_curve_items_parity(p, nc, ns, dim, shuffle):
     run_case(cb, derivs=False)
 
 
+@pytest.mark.parametrize("spans", [63, 64, 65, 128])
+def test_as_many_spans_as_lanes(spans):
+    # every span holds samples, one item each at least: the item length has to
+    # exist where spans and lanes are equal in number
+    cb = W.curve_batch(seed=spans, B=2, p=1, nc=spans + 1, ns=300, dim=2)
+    cb.knots[:] = W.clamped_uniform_knots(spans + 1, 1)
+    run_case(cb, derivs=False)
+
+
 def test_one_parameter_for_all_samples_and_order_invariance():
     cb = W.curve_batch(seed=1, B=2, p=3, nc=12, ns=300, dim=3, shared_u=False)
     cb.us[0] = cb.us[0, 150]
