@@ -33,7 +33,7 @@
 // slots in a fixed order, so results are bitwise reproducible and do not
 // depend on which wave ran which tile.
 //
-// Finalize, one wave per surface: dL/dPw = sum of tile rectangles;
+// Finalize, in parts of a surface: dL/dPw = sum of tile rectangles;
 // dL/dP = w dL/dPw_xyz, dL/dw = P . dL/dPw_xyz + dL/dPw_w; dL/dU_k by the
 // reverse-mode knot derivative of each row's basis weighted with e(a)
 // (Sec. 3.2.1), dL/dV_k likewise with f(b).
@@ -1074,7 +1074,7 @@ __device__ __forceinline__ void bwd_tile(const Surf& sg, int q, int col0, int ro
 }
 
 // --------------------------------------------------------------------------
-// finalize: one wave per surface (kWavesPerWG surfaces per workgroup)
+// finalize: parts of a surface, a wave (or, for a knot vector, a workgroup) each
 // --------------------------------------------------------------------------
 constexpr int kFinCp = 4;         // plans: control points per lane per pass (registers for six waves/SIMD)
 constexpr int kFinW = 2 * kMaxDeg + 2;

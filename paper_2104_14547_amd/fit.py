@@ -20,9 +20,8 @@ with a precomputed basis) and every step reads them
 
 The fit owns a library context whose tiling (sample points per forward and
 backward tile) is chosen at construction by timing the candidates on the
-problem itself (``tiling="auto"``): one surface of 512 x 512 samples makes
-only 16 tiles at the default 16384 points per tile, far too few waves for
-the chip.  The summation order, and so the bits of the result, depend on
+problem itself (``tiling="auto"``): the library's default backward tiles (about
+72 rows, the same for every batch) are longer than is best for one surface.  The summation order, and so the bits of the result, depend on
 the tiling only.
 
 With ``graph=True`` the whole step (both library launches, the loss gradient,
