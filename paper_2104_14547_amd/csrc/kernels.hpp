@@ -1334,7 +1334,7 @@ __device__ __forceinline__ void fin_knots_u(const Surf& s, int ntiles, TileAt ti
 #pragma unroll
         for (int r = 0; r <= P; ++r) e[r] = 0.0f;
         const int rb = a / rows;
-#pragma unroll(NW > 1 ? 4 : 1)
+#pragma unroll(NW > 1 ? 4 : 2)
         for (int cb = 0; cb < ncb; ++cb) {
             const TileRef tr = tile_at(rb * ncb + cb);
             const float* ev = reinterpret_cast<const float*>(tr.slot + kSlotHead + rect_bytes) +
@@ -1358,8 +1358,10 @@ __device__ __forceinline__ void fin_knots_v(const Surf& s, int ntiles, TileAt ti
 #pragma unroll
         for (int h = 0; h <= Q; ++h) f[h] = 0.0f;
         const int cb = b / kWave;
-        // several row blocks' loads in flight; added in order
-#pragma unroll(NW > 1 ? (Q <= 3 ? 8 : 4) : 1)
+        // several row blocks' loads in flight; added in order (two in plans,
+        // whose registers hold no more: finalize of 4096 uneven surfaces 39.0
+        // us, one at a time 40.0)
+#pragma unroll(NW > 1 ? (Q <= 3 ? 8 : 4) : 2)
         for (int rb = 0; rb < nrb; ++rb) {
             const TileRef tr = tile_at(rb * ncb + cb);
             const float* fv = reinterpret_cast<const float*>(
