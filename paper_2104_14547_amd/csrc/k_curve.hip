@@ -363,6 +363,46 @@ struct CurveSample {
     }
 };
 
+// The scan over the wave multiplies what comes from another run by 0, which a
+// NaN or an infinity survives: then the wave takes a scan that selects, so such
+// a value reaches its own span's sums and no others.
+template <int P1, int K>
+__device__ __forceinline__ bool wave_finite(const float4 (&c)[P1], const float (&g)[K]) {
+    float z = 0.f;
+#pragma unroll
+    for (int r = 0; r < P1; ++r)
+        z = __builtin_fmaf(c[r].x, 0.f, __builtin_fmaf(c[r].y, 0.f,
+            __builtin_fmaf(c[r].z, 0.f, __builtin_fmaf(c[r].w, 0.f, z))));
+#pragma unroll
+    for (int t = 0; t < K; ++t) z = __builtin_fmaf(g[t], 0.f, z);
+    return __ballot(z != 0.f) == 0ull;
+}
+
+template <int P1, int K>
+__device__ __forceinline__ void seg_scan_select(float4 (&c)[P1], float (&g)[K], const Runs& rn) {
+    const int lane = lane_id();
+    // first lane of the run: the one after the last run end below this lane
+    const unsigned long long ends = __ballot(rn.head) & ((1ull << lane) - 1ull);
+    const int first = ends ? kWave - __builtin_clzll(ends) : 0;
+#pragma unroll 1
+    for (int d = 1; d < kWave; d <<= 1) {
+        const bool in = lane - d >= first;
+        auto step = [&](float& x) {
+            const float y = __shfl_up(x, d);
+            if (in) x += y;
+        };
+#pragma unroll
+        for (int r = 0; r < P1; ++r) {
+            step(c[r].x);
+            step(c[r].y);
+            step(c[r].z);
+            step(c[r].w);
+        }
+#pragma unroll
+        for (int t = 0; t < K; ++t) step(g[t]);
+    }
+}
+
 // What bounds it: VALU issue of the per-sample work (basis, curve point,
 // adjoint): about 150 instructions a step, 7.0e7 wave instructions (113 us of
 // issue) for 16384 cubic space curves of 32 control points x 1024 samples,
@@ -438,6 +478,7 @@ __global__ void __launch_bounds__(W* kWave) k_curve_bwd(CurveArgs a, const float
             const CurveSample<DIM> x = nx;
             const int ni = min(i + m, j1 - 1);
             nx.load(l.us, g0, in_order ? ni : (int)l.perm[ni]);
+            if (i >= j1 || !act) continue;  // no sample for this lane
             const float u = x.u;
             float N[P + 1], st[P * (P + 1) / 2];
             span_basis<P>(K, inv, u, N, st);
@@ -451,8 +492,7 @@ __global__ void __launch_bounds__(W* kWave) k_curve_bwd(CurveArgs a, const float
                 if constexpr (DIM == 3) C[2] = __builtin_fmaf(Nw[r], q[r].z, C[2]);
             }
             const float ic = recip(Wsum);
-            const float iw = i < j1 && act ? ic : 0.f;  // 0: no sample, no contribution
-            const float h[3] = {x.g[0] * iw, x.g[1] * iw, x.g[2] * iw};
+            const float h[3] = {x.g[0] * ic, x.g[1] * ic, x.g[2] * ic};
 #pragma unroll
             for (int d = 0; d < DIM; ++d) C[d] *= ic;
             float e[P + 1];
@@ -475,11 +515,15 @@ __global__ void __launch_bounds__(W* kWave) k_curve_bwd(CurveArgs a, const float
         // of each run adds the run's sums; for a fixed r the run ends touch
         // distinct control points
         const Runs rn = wave_runs(act ? k : kSentinel);
+        if (wave_finite(c4, gU)) {
 #pragma unroll
-        for (int r = 0; r <= P; ++r) seg_scan4(c4[r], rn);
-        if (want_k) {
+            for (int r = 0; r <= P; ++r) seg_scan4(c4[r], rn);
+            if (want_k) {
 #pragma unroll
-            for (int t = 0; t < 2 * P; t += 2) seg_scan2(gU[t], gU[t + 1], rn);
+                for (int t = 0; t < 2 * P; t += 2) seg_scan2(gU[t], gU[t + 1], rn);
+            }
+        } else {
+            seg_scan_select(c4, gU, rn);
         }
         const bool wr = rn.head && act;
 #pragma unroll

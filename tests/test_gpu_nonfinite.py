@@ -1,0 +1,62 @@
+"""How far a non-finite dL/dC of a curve reaches: the control points and knots
+of its sample's own span and no others, whatever the samples' order, and an
+infinity stays one where the sums hold no other."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import paper_2104_14547_amd as nd  # noqa: E402
+from paper_2104_14547_amd import workloads as W  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+def T(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to(torch.device("cuda", 0))
+
+
+def spans_of(U, us, p):
+    nc = len(U) - p - 1
+    return np.clip(np.searchsorted(U, us, side="right") - 1, p, nc - 1)
+
+
+@pytest.mark.parametrize("shuffle", [False, True])
+@pytest.mark.parametrize("p,nc,ns,dim", [(3, 32, 1024, 3), (2, 9, 70, 2), (1, 60, 3000, 3), (5, 40, 385, 2)])
+def test_nan_stays_with_its_span(p, nc, ns, dim, shuffle):
+    cb = W.curve_batch(seed=p + ns, B=2, p=p, nc=nc, ns=ns, dim=dim, shared_u=False, shuffle=shuffle)
+    args = [T(x) for x in (cb.ctrl, cb.w, cb.knots)]
+    s = ns // 2
+    k = int(spans_of(cb.knots[0], cb.us[0], p)[s])
+    runs = {}
+    for name, v in (("clean", cb.upstream[0, s, 0]), ("zero", 0.0), ("nan", np.nan)):
+        g = cb.upstream.copy()
+        g[0, s] = v if name != "clean" else g[0, s]
+        runs[name] = [x.cpu().numpy() for x in nd.api.curve_bwd(*args, p, T(cb.us), T(g))]
+    lo_hi = ((k - p, k + 1), (k - p, k + 1), (k - p + 1, k + p + 1))  # control points, weights, knots
+    for clean, zero, nan, (lo, hi) in zip(runs["clean"], runs["zero"], runs["nan"], lo_hi):
+        assert np.array_equal(nan[1], clean[1])
+        out = np.ones(zero.shape[1], bool)
+        out[lo:hi] = False
+        assert np.isnan(nan[0][~out]).any()
+        assert np.isfinite(nan[0][out]).all()
+        # the sums of the other spans are the same terms, in another order at most
+        assert np.abs(nan[0][out] - zero[0][out]).max(initial=0) <= 1e-4 * np.abs(zero[0]).max()
+
+
+@pytest.mark.parametrize("shuffle", [False, True])
+@pytest.mark.parametrize("p,nc,ns,dim", [(3, 12, 300, 3), (2, 5, 1000, 2), (1, 3, 2500, 3)])
+def test_infinity_at_the_last_sample_of_every_span(p, nc, ns, dim, shuffle):
+    cb = W.curve_batch(seed=ns, B=2, p=p, nc=nc, ns=ns, dim=dim, shared_u=False, shuffle=shuffle, repeat=0.0)
+    cb.knots[:] = W.clamped_uniform_knots(nc, p)
+    g = cb.upstream.copy()
+    for c in range(2):
+        k = spans_of(cb.knots[c], cb.us[c], p)
+        for span in np.unique(k):
+            at = np.flatnonzero(k == span)
+            # the last in parameter for sorted samples, the last in input order otherwise
+            g[c, at[-1], 0] = np.inf
+    gc = nd.api.curve_bwd(*[T(x) for x in (cb.ctrl, cb.w, cb.knots)], p, T(cb.us), T(g))[0].cpu().numpy()
+    # every basis function is positive strictly inside its spans
+    assert np.isposinf(gc[..., 0]).all()
+    assert np.isfinite(gc[..., 1:]).all()
