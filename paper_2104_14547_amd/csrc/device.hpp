@@ -301,7 +301,9 @@ __device__ __forceinline__ void span_adjoint(const float* K, const float* inv, f
             const int lo = D - 1 - d + m, hi = D - 1 + m;
             const float xl = x - K[lo], hx = K[hi] - x;
             const float a = A[m], b = A[m - 1];
-            const float c = s[tri(d, m)] * inv[tri(d, m)] * (b - a);
+            // in this order: the square of inv can leave the float range
+            // where the product with b - a does not
+            const float c = s[tri(d, m)] * (b - a) * inv[tri(d, m)];
             gK[lo] = __builtin_fmaf(c, hx, gK[lo]);
             gK[hi] = __builtin_fmaf(c, xl, gK[hi]);
             A[m - 1] = inv[tri(d, m)] * __builtin_fmaf(a, xl, b * hx);
