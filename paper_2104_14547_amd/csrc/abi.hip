@@ -100,17 +100,32 @@ int check_shape(nurbs_ctx* c, int p, int q, int nu_c, int nv_c, int nu_s, int nv
     return NURBS_OK;
 }
 
-// Rows per tile from the surface's own shape only, so that a surface gets
-// the same tiling -- and bitwise the same result -- alone, in a uniform
-// batch or in any ragged mix.  A tile is one wave64 over min(64, nv_s)
-// columns; the row count aims at a fixed number of points per tile.
-// Rows of a backward tile when the caller set none (nurbs_ctx_set_tiling), in
-// uniform batches and plans alike: the surface's rows in equal parts of about
-// kDefaultRows.  The rows fix the order of the sums, and a surface's gradients
-// depend neither on its batch nor on the kind of call, so the rule looks at
-// its rows alone.  A tile's rows run one after the other (about 0.45 us each),
-// so the longest tile bounds a small batch; more tiles cost a full chip a
-// set-up and p + 1 more flushed control rows each.  Forward and backward of
+// Rows of a tile of target_pts sample points (nurbs_ctx_set_tiling), from the
+// surface's own sample grid only: a tile is one wave64 over min(64, nv_s)
+// columns.
+int tile_rows(int nu_s, int nv_s, int target_pts) {
+    const int cols = std::max(1, std::min(kWave, nv_s));
+    const int rows = std::max(1, target_pts / cols);
+    return std::max(1, std::min(std::max(nu_s, 1), rows));
+}
+
+// Bytes of a surface's backward slots with `rows` sample rows to a tile.
+size_t slots_bytes(int p, int q, int nu_c, int nv_c, int nu_s, int nv_s, int rows) {
+    return (size_t)((nv_s + kWave - 1) / kWave) * ((nu_s + rows - 1) / rows) * slot_bytes(p, q, nu_c, nv_c, rows);
+}
+
+constexpr size_t kWsHeader = 256;  // error word + padding
+// What the built-in scratch's limit and the server count in.
+constexpr int kDefaultTilePts = 16384;
+constexpr size_t kNoAllocScratchBytes = size_t(64) << 20;  // the built-in scratch
+
+// Rows of a backward tile when the caller set none, in uniform batches and
+// plans alike: the surface's rows in equal parts of about kDefaultRows.  The
+// rows fix the order of the sums, and a surface's gradients depend neither on
+// its batch nor on the kind of call, so the rule looks at its shape alone.  A
+// tile's rows run one after the other (about 0.45 us each), so the longest
+// tile bounds a small batch; more tiles cost a full chip a set-up and p + 1
+// more flushed control rows each.  Forward and backward of
 // uneven batches of n surfaces, kernel time in us by rows per tile (equal
 // parts; the last column 16384 points, up to 256 rows and more):
 //   n       48    56    64    72    80    96   256
@@ -120,14 +135,26 @@ int check_shape(nurbs_ctx* c, int p, int q, int nu_c, int nv_c, int nu_s, int nv
 //   64     110   110   110   110   108   153   206
 // (parts of 64 rows and a remainder: 469, 172, 135, 102).  The backward of one
 // bicubic 512 x 512 surface: 49 at 64 rows, 134 at 256.
+//
+// Every tile has a slot that holds a whole net, so the slots have a budget:
+// the built-in scratch, or what tiles of 16384 points take where that is more.
+// A surface whose parts exceed it takes fewer and longer ones.
 constexpr int kDefaultRows = 72;
-// What the built-in scratch's limit and the server count in.
-constexpr int kDefaultTilePts = 16384;
 
-int tile_rows(int nu_s, int nv_s, int target_pts) {
-    const int cols = std::max(1, std::min(kWave, nv_s));
-    const int rows = std::max(1, target_pts / cols);
-    return std::max(1, std::min(std::max(nu_s, 1), rows));
+int default_rows(int p, int q, int nu_c, int nv_c, int nu_s, int nv_s) {
+    if (nu_s < 1) return 1;
+    auto parts_of = [&](int n) { return (nu_s + n - 1) / n; };
+    auto bytes = [&](int rows) { return slots_bytes(p, q, nu_c, nv_c, nu_s, nv_s, rows); };
+    int rows = parts_of(std::max(1, (int)(((long long)nu_s + kDefaultRows / 2) / kDefaultRows)));
+    const int coarse = tile_rows(nu_s, nv_s, kDefaultTilePts);
+    const size_t budget = std::max(bytes(coarse), kNoAllocScratchBytes - kWsHeader);
+    if (bytes(rows) <= budget || rows >= coarse) return rows;
+    int hi = coarse;  // rows exceed the budget, hi do not
+    while (hi - rows > 1) {
+        const int mid = rows + (hi - rows) / 2;
+        if (bytes(mid) > budget) rows = mid; else hi = mid;
+    }
+    return parts_of(parts_of(hi));  // as many tiles, of equal length
 }
 
 }  // namespace
@@ -217,10 +244,8 @@ int nurbs_ctx_device_info(nurbs_ctx* ctx, int* num_cus, int* wave_size) {
 // --------------------------------------------------------------------------
 namespace {
 
-int rows_bwd(const nurbs_ctx* c, int nu_s, int nv_s) {
-    if (c->bwd_tile_pts) return tile_rows(nu_s, nv_s, c->bwd_tile_pts);
-    const int parts = std::max(1, (nu_s + kDefaultRows / 2) / kDefaultRows);
-    return std::max(1, (nu_s + parts - 1) / parts);
+int rows_bwd(const nurbs_ctx* c, int p, int q, int nu_c, int nv_c, int nu_s, int nv_s) {
+    return c->bwd_tile_pts ? tile_rows(nu_s, nv_s, c->bwd_tile_pts) : default_rows(p, q, nu_c, nv_c, nu_s, nv_s);
 }
 
 struct UniformGeom {
@@ -252,7 +277,7 @@ UniformGeom uniform_geom(const nurbs_ctx* c, int B, int p, int q, int nu_c, int 
     const long long cols = (long long)B * g.ncb;
     g.rows_f = c->fwd_tile_pts ? tile_rows(nu_s, nv_s, c->fwd_tile_pts)
                                : auto_rows_fwd(std::max(c->num_cus, 1), cols * nu_s, std::max(nu_s, 1));
-    g.rows_b = rows_bwd(c, nu_s, nv_s);
+    g.rows_b = rows_bwd(c, p, q, nu_c, nv_c, nu_s, nv_s);
     g.nrb_f = (nu_s + g.rows_f - 1) / g.rows_f;
     g.nrb_b = (nu_s + g.rows_b - 1) / g.rows_b;
     g.tiles_f = cols * g.nrb_f;
@@ -263,7 +288,6 @@ UniformGeom uniform_geom(const nurbs_ctx* c, int B, int p, int q, int nu_c, int 
     return g;
 }
 
-constexpr size_t kWsHeader = 256;  // error word + padding
 // plan workspaces: the 256-byte header, then the dynamic schedule's tile
 // counters of the forward and of the backward (kQueues each, 128 bytes apart)
 constexpr size_t kQueueFwd = kWsHeader;
@@ -584,7 +608,6 @@ namespace {
 // process ends.  Host code must never pass `scratch` itself to a kernel
 // (in host code it is a stand-in, not a device address): it uses the
 // per-device address from hipGetSymbolAddress below.
-constexpr size_t kNoAllocScratchBytes = size_t(64) << 20;
 static __device__ __align__(256) char scratch[kNoAllocScratchBytes];
 
 constexpr int kMaxDevices = 64;
@@ -626,8 +649,7 @@ int nurbs_surface_bwd_noalloc(nurbs_ctx* ctx, int B, int p, int q, int nu_c, int
     // the limit counts every surface's slots in tiles of 16384 points (or the
     // caller's), whatever tiles and groups the call then takes
     const int rows = tile_rows(nu_s, nv_s, ctx->bwd_tile_pts ? ctx->bwd_tile_pts : kDefaultTilePts);
-    const size_t tiles = (size_t)B * ((nv_s + kWave - 1) / kWave) * ((nu_s + rows - 1) / rows);
-    const size_t need = grad_mask ? kWsHeader + tiles * slot_bytes(p, q, nu_c, nv_c, rows) : 0;
+    const size_t need = grad_mask ? kWsHeader + (size_t)B * slots_bytes(p, q, nu_c, nv_c, nu_s, nv_s, rows) : 0;
     if (need > kNoAllocScratchBytes)
         return fail(ctx, NURBS_EWORKSPACE,
                     "this backward needs " + std::to_string(need) + " bytes of scratch; the built-in scratch holds " +
@@ -1016,7 +1038,7 @@ int plan_build(nurbs_ctx* ctx, const nurbs_desc* host, int n, unsigned flags, nu
         const int ncb = (d.nv_s + kWave - 1) / kWave;
         const int rf = ctx->fwd_tile_pts ? tile_rows(d.nu_s, d.nv_s, ctx->fwd_tile_pts)
                                          : auto_rows_fwd(cus, col_rows, std::max(d.nu_s, 1));
-        const int rb = rows_bwd(ctx, d.nu_s, d.nv_s);
+        const int rb = rows_bwd(ctx, d.p, d.q, d.nu_c, d.nv_c, d.nu_s, d.nv_s);
         x.rows = rb;
         x.tile_first = (int)bt.size();
         x.slot0 = (long long)(kPlanHeader + slot_off);
