@@ -136,18 +136,29 @@ constexpr size_t kNoAllocScratchBytes = size_t(64) << 20;  // the built-in scrat
 // (parts of 64 rows and a remainder: 469, 172, 135, 102).  The backward of one
 // bicubic 512 x 512 surface: 49 at 64 rows, 134 at 256.
 //
-// Every tile has a slot that holds a whole net, so the slots have a budget:
-// the built-in scratch, or what tiles of 16384 points take where that is more.
-// A surface whose parts exceed it takes fewer and longer ones.
-constexpr int kDefaultRows = 72;
+// Grids of up to kNarrow columns leave most of a wave's lanes idle and move few
+// points per slot, so their tiles are longer: 4096 bicubic surfaces of 256 x 3
+// samples on 10 x 10 nets 285 us a backward at 64 rows, 261 at 128 and at 256;
+// 1024 of degree 5 with 256 x 8 on 40 x 40 195, 175, 222; 64 of 4096 x 8 on 48 x
+// 48 135, 135, 173; one of those 85, 111, 162 (1606 at 4096 rows).
+//
+// Every tile has a slot that holds a whole net, so the slots of a surface have
+// a budget: kSlotShare times its points' bytes and a MiB, at most the built-in
+// scratch, or what tiles of 16384 points take where that is more.  A surface
+// whose parts exceed it takes fewer and longer ones (one of 100000 x 1 samples
+// on a 16 x 16 net: 20 MB of slots instead of 30).
+constexpr int kDefaultRows = 72, kNarrowRows = 128, kNarrow = 8;
+constexpr size_t kSlotShare = 16;
 
 int default_rows(int p, int q, int nu_c, int nv_c, int nu_s, int nv_s) {
     if (nu_s < 1) return 1;
     auto parts_of = [&](int n) { return (nu_s + n - 1) / n; };
     auto bytes = [&](int rows) { return slots_bytes(p, q, nu_c, nv_c, nu_s, nv_s, rows); };
-    int rows = parts_of(std::max(1, (int)(((long long)nu_s + kDefaultRows / 2) / kDefaultRows)));
+    const int aim = nv_s <= kNarrow ? kNarrowRows : kDefaultRows;
+    int rows = parts_of(std::max(1, (int)(((long long)nu_s + aim / 2) / aim)));
     const int coarse = tile_rows(nu_s, nv_s, kDefaultTilePts);
-    const size_t budget = std::max(bytes(coarse), kNoAllocScratchBytes - kWsHeader);
+    const size_t share = kSlotShare * 3 * sizeof(float) * nu_s * nv_s + (size_t(1) << 20);
+    const size_t budget = std::max(bytes(coarse), std::min(kNoAllocScratchBytes - kWsHeader, share));
     if (bytes(rows) <= budget || rows >= coarse) return rows;
     int hi = coarse;  // rows exceed the budget, hi do not
     while (hi - rows > 1) {
