@@ -150,6 +150,10 @@ constexpr size_t kNoAllocScratchBytes = size_t(64) << 20;  // the built-in scrat
 constexpr int kDefaultRows = 72, kNarrowRows = 128, kNarrow = 8;
 constexpr size_t kSlotShare = 16;
 
+size_t slots_share(int nu_s, int nv_s) {
+    return kSlotShare * 3 * sizeof(float) * nu_s * nv_s + (size_t(1) << 20);
+}
+
 int default_rows(int p, int q, int nu_c, int nv_c, int nu_s, int nv_s) {
     if (nu_s < 1) return 1;
     auto parts_of = [&](int n) { return (nu_s + n - 1) / n; };
@@ -157,8 +161,8 @@ int default_rows(int p, int q, int nu_c, int nv_c, int nu_s, int nv_s) {
     const int aim = nv_s <= kNarrow ? kNarrowRows : kDefaultRows;
     int rows = parts_of(std::max(1, (int)(((long long)nu_s + aim / 2) / aim)));
     const int coarse = tile_rows(nu_s, nv_s, kDefaultTilePts);
-    const size_t share = kSlotShare * 3 * sizeof(float) * nu_s * nv_s + (size_t(1) << 20);
-    const size_t budget = std::max(bytes(coarse), std::min(kNoAllocScratchBytes - kWsHeader, share));
+    const size_t budget =
+        std::max(bytes(coarse), std::min(kNoAllocScratchBytes - kWsHeader, slots_share(nu_s, nv_s)));
     if (bytes(rows) <= budget || rows >= coarse) return rows;
     int hi = coarse;  // rows exceed the budget, hi do not
     while (hi - rows > 1) {
@@ -264,11 +268,17 @@ struct UniformGeom {
     long long tiles_f;
     int tiles_b;        // backward tiles of one surface
     size_t slot;        // bytes of a backward tile's slot
+    size_t one;         // bytes of one surface's slots
     int group;          // surfaces the backward takes at a time (its workspace holds their slots)
 };
 
 // Most workspace the backward's slots take unless one surface needs more.
 constexpr size_t kGroupBytes = size_t(1) << 30;
+
+// Workspace for B surfaces of `one` bytes taken in groups.  In bytes, not in
+// whole surfaces, so that it grows with both and a workspace sized for a
+// larger call serves a smaller one.
+size_t group_ws(size_t B, size_t one) { return std::max(one, std::min(B * one, kGroupBytes)); }
 
 // Rows of a forward tile when the caller set none.  A point's bits do not
 // depend on the tile it is in, so the rows may follow the batch: enough tiles
@@ -294,9 +304,23 @@ UniformGeom uniform_geom(const nurbs_ctx* c, int B, int p, int q, int nu_c, int 
     g.tiles_f = cols * g.nrb_f;
     g.tiles_b = g.ncb * g.nrb_b;
     g.slot = slot_bytes(p, q, nu_c, nv_c, g.rows_b);
-    const size_t one = std::max<size_t>(1, (size_t)g.tiles_b * g.slot);
-    g.group = (int)std::max<long long>(1, std::min<long long>(B, (long long)(kGroupBytes / one)));
+    g.one = (size_t)g.tiles_b * g.slot;
+    g.group = (int)(group_ws(std::max(B, 1), g.one) / std::max<size_t>(1, g.one));
     return g;
+}
+
+// Bytes of slots to ask for per surface: no less for a shape that is larger in
+// any of its sizes.  Under the default tiles the exact bytes are not such a
+// number, because rows are rounded up to equal parts.
+size_t slots_asked(const nurbs_ctx* c, const UniformGeom& g, int p, int q, int nu_c, int nv_c, int nu_s, int nv_s) {
+    if (c->bwd_tile_pts || nu_s < 1) return g.one;
+    const size_t tile = slot_bytes(p, q, nu_c, nv_c, 0) + 16, row = sizeof(float) * (size_t)(p + 1);
+    const int aim = nv_s <= kNarrow ? kNarrowRows : kDefaultRows, coarse = tile_rows(nu_s, nv_s, kDefaultTilePts);
+    // parts of fewer than 2 kNarrowRows rows; the last tile's are counted whole
+    const size_t fine = g.ncb * (tile * std::max<size_t>(1, ((size_t)nu_s + aim / 2) / aim) +
+                                 row * ((size_t)nu_s + 2 * kNarrowRows));
+    const size_t most = g.ncb * (tile * (((size_t)nu_s + coarse - 1) / coarse) + row * 2 * nu_s);
+    return std::max(most, std::min(fine, std::min(kNoAllocScratchBytes - kWsHeader, slots_share(nu_s, nv_s))));
 }
 
 // plan workspaces: the 256-byte header, then the dynamic schedule's tile
@@ -342,7 +366,7 @@ int nurbs_surface_ws_bytes(nurbs_ctx* ctx, int B, int p, int q, int nu_c, int nv
         return NURBS_OK;
     }
     const UniformGeom g = uniform_geom(ctx, B, p, q, nu_c, nv_c, nu_s, nv_s);
-    *out = kWsHeader + (size_t)g.group * g.tiles_b * g.slot;
+    *out = kWsHeader + group_ws(B, slots_asked(ctx, g, p, q, nu_c, nv_c, nu_s, nv_s));
     return NURBS_OK;
 }
 
@@ -409,10 +433,9 @@ hipError_t launch_uniform_gather(const nurbs_ctx* ctx, hipStream_t st, const Uni
 // The workspace has to hold the slots of a group of surfaces; `fit` takes
 // smaller groups instead where it does not (the built-in scratch).
 int check_bwd_ws(nurbs_ctx* ctx, UniformGeom& g, int B, int nu_c, int nv_c, const void* ws, size_t ws_bytes, bool fit) {
-    const size_t one = (size_t)g.tiles_b * g.slot;
     if (fit && ws_bytes > kWsHeader)
-        g.group = (int)std::max<size_t>(1, std::min<size_t>(g.group, (ws_bytes - kWsHeader) / std::max<size_t>(1, one)));
-    const size_t need = kWsHeader + g.group * one;
+        g.group = (int)std::max<size_t>(1, std::min<size_t>(g.group, (ws_bytes - kWsHeader) / std::max<size_t>(1, g.one)));
+    const size_t need = kWsHeader + (fit ? g.group * g.one : group_ws(B, g.one));
     if (!ws || ws_bytes < need) return fail(ctx, NURBS_EWORKSPACE, "workspace too small: need " + std::to_string(need));
     if ((long long)g.group * g.tiles_b > (1ll << 30) || (long long)B * fin_parts(nu_c, nv_c) > (1ll << 30) ||
         (long long)g.group * (2 + (nu_c * nv_c + kWave - 1) / kWave) > (1ll << 30))
