@@ -301,11 +301,13 @@ int nurbs_surface_uv_fwd(nurbs_ctx *ctx, int B, int p, int q, int nu_c, int nv_c
 
 /* Vector-Jacobian product at the pairs (Sec. 3.2 at each pair); outputs
  * and grad_mask as nurbs_surface_bwd.  Each gradient entry is a sum over
- * pairs in arbitrary order.  With at least as many pairs as the net has
- * cells ((nu_c - p)(nv_c - q), at most 4096 of them) the pairs are ordered by
- * cell, keeping the input's order within a cell, and summed in FP64 in that
- * order.  Otherwise, and when ws holds fewer bytes than that needs (it was
- * sized for fewer pairs), the terms are added exactly: each is rounded to a
+ * pairs in arbitrary order.  With enough pairs to a cell of the net (a pair
+ * of knot spans; (nu_c - p)(nv_c - q) of them, at most 4096) the pairs are
+ * ordered by cell, keeping the input's order within a cell, and summed in FP64
+ * in that order: at least 32 pairs to a cell on average (and 384 / ((p+1)(q+1)))
+ * for nets of up to about 1800 control points, one (and 8 / ((p+1)(q+1))) for
+ * larger ones.  Otherwise, and when ws holds fewer bytes than that needs (it
+ * was sized for fewer pairs), the terms are added exactly: each is rounded to a
  * multiple of 2^-s (2^s the largest power of two with npts times the largest
  * term of that gradient tensor at most 2^62) and summed as 64-bit integers,
  * which adds at most npts * max|term| * 2^-63 per entry.  Both are bitwise

@@ -14,10 +14,10 @@
 //   e_i = sum_j N_j w_ij (P_ij - S) . g / W = dL/dN_i(u)  (eq. NURBSvDerivative6)
 // and f_j likewise, through the knot adjoint of the recursion (Sec. 3.2.1).
 // The pairs come in any order, so one control point collects terms from
-// pairs anywhere in the input.  Where a cell of the net holds a pair or more
-// on average the pairs are ordered by cell first (k_uv_cells.hip).  Nets of
-// more cells than pairs, or of more cells than that ordering counts in LDS,
-// and workspaces too small for its tables take the path here.  Terms are
+// pairs anywhere in the input.  Where the cells of the net hold enough pairs
+// on average the pairs are ordered by cell first (k_uv_cells.hip, which says
+// where the line lies).  Fewer pairs, nets of more cells than that ordering
+// counts in LDS, and workspaces too small for its tables take the path here.  Terms are
 // summed exactly instead of in a fixed order: k_uv_max finds, per surface and gradient tensor, the largest
 // magnitude of a single term; k_uv_acc recomputes every term, rounds it to a
 // multiple of 2^-s, with 2^s chosen so that npts times the largest term

@@ -563,13 +563,22 @@ bool uv_sort_plan(int B, int p, int q, int nu_c, int nv_c, int npts, size_t head
     UvSort s{};
     s.ncv = nv_c - q;
     const long long cells = (long long)(nu_c - p) * s.ncv;
-    // Where the line lies: below one pair to a cell on average an item's sums
-    // (one slot per cell, read back by every control point) cost more than a
-    // few atomics per pair: 64 surfaces of degree (5, 5), 40 x 40 net and 1000
-    // pairs (1225 cells) take 220 us a pass here and 166 us with the atomics;
-    // with 30000 pairs (B = 8, 48 x 48 net) 188 us here and 3.8 ms there.
+    // Where the line lies.  An item costs a wave's pass however few pairs it
+    // has, so a full chip wants cells of many pairs; against accumulators in LDS
+    // (kUvLdsAccMax) the atomic path is the better one below about 32 to a
+    // cell, and at low degrees, where a pair has few atomics, below more.  64
+    // surfaces of degree (4, 1), 42 x 13 net: 4095 pairs (9 to a cell) 129 us
+    // here, 71 there; (4, 5), 36 x 30, 6618 pairs (8): 244, 150; (2, 4), 19 x 35,
+    // 13058 (25): 200, 163; 256 of (3, 3), 16 x 16, 64 to a cell: 238, 411; 256 of
+    // (1, 1), 16 x 16, 64 and 256 to a cell: 202, 173 and 408, 581 (a single
+    // surface gains from about one pair to a cell on, but what decides must
+    // not depend on the batch).  Accumulators in global memory: one pair to a
+    // cell is enough (8 surfaces of (3, 3), 60 x 60: 83 us, 184), at degree
+    // (1, 1) two (one surface: 58 us, 64; with one pair to a cell 56, 45).
     // Above kUvCellsMax cells the counters of a chunk outgrow their LDS.
-    if (npts < 1 || cells > kUvCellsMax || npts < cells) return false;
+    const long long terms = (p + 1) * (q + 1), nacc = 4ll * nu_c * nv_c + nu_c + nv_c + p + q + 2;
+    const long long least = nacc <= kUvLdsAccMax ? std::max(32ll, 384 / terms) : std::max(1ll, 8 / terms);
+    if (npts < 1 || cells > kUvCellsMax || npts < least * cells) return false;
     s.cells = (int)cells;
     // nothing that fixes the order of a sum depends on B, so that a surface's
     // result does not depend on the batch it is in
