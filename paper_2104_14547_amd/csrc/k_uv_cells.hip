@@ -100,14 +100,17 @@ __global__ void __launch_bounds__(kWG) k_uv_hist(UvArgs a, UvSort s, SortPtrs t,
     for (int i = tid; i < s.cells; i += kWG) o[i] = hist[i];
 }
 
-// One workgroup per surface.  cells <= kUvCellsMax = 4 kScanWG.
-constexpr int kScanWG = 1024;
-__global__ void __launch_bounds__(kScanWG) k_uv_scan(UvSort s, SortPtrs t) {
-    __shared__ int tot[kUvCellsMax];
-    __shared__ int2 wsum[kScanWG / kWave];
+// One workgroup per surface, of four waves up to 1024 cells (2000 surfaces of 9
+// cells: 59 us with sixteen), sixteen beyond.  cells <= 4 WG <= kUvCellsMax.
+constexpr int kScanPer = 4;
+template <int WG>
+__global__ void __launch_bounds__(WG) k_uv_scan(UvSort s, SortPtrs t) {
+    constexpr int kCells = kScanPer * WG;
+    __shared__ int tot[kCells];
+    __shared__ int2 wsum[WG / kWave];
     const int g = blockIdx.x, tid = threadIdx.x;
     unsigned* h = t.hist + (size_t)g * s.nchunk * s.cells;
-    for (int c = tid; c < kUvCellsMax; c += kScanWG) {
+    for (int c = tid; c < kCells; c += WG) {
         unsigned run = 0;
         if (c < s.cells) {
             constexpr int kU = 32;  // chunks in flight
@@ -127,11 +130,10 @@ __global__ void __launch_bounds__(kScanWG) k_uv_scan(UvSort s, SortPtrs t) {
     }
     __syncthreads();
     // exclusive prefix of (pairs, items) over the cells, four per thread
-    constexpr int kPer = kUvCellsMax / kScanWG;
-    int n[kPer], sum = 0, isum = 0;
+    int n[kScanPer], sum = 0, isum = 0;
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-        n[i] = tot[tid * kPer + i];
+    for (int i = 0; i < kScanPer; ++i) {
+        n[i] = tot[tid * kScanPer + i];
         sum += n[i];
         isum += (n[i] + s.seg - 1) / s.seg;
     }
@@ -154,8 +156,8 @@ __global__ void __launch_bounds__(kScanWG) k_uv_scan(UvSort s, SortPtrs t) {
     int* is = t.item_start + (size_t)g * (s.cells + 1);
     int* ic = t.item_cell + (size_t)g * s.items;
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-        const int c = tid * kPer + i;
+    for (int i = 0; i < kScanPer; ++i) {
+        const int c = tid * kScanPer + i;
         if (c <= s.cells) {
             cs[c] = at;
             is[c] = it;
@@ -165,7 +167,7 @@ __global__ void __launch_bounds__(kScanWG) k_uv_scan(UvSort s, SortPtrs t) {
         at += n[i];
         it += ni;
     }
-    if (tid == kScanWG - 1 && s.cells == kUvCellsMax) {
+    if (tid == WG - 1 && s.cells == kCells) {
         cs[s.cells] = at;
         is[s.cells] = it;
     }
@@ -494,7 +496,9 @@ __global__ void __launch_bounds__(kWG) k_uv_cell(UvArgs a, UvSort s, SortPtrs t,
 __device__ __forceinline__ double cell_sum(const int* __restrict__ is, const double* __restrict__ slots, int slot,
                                            int c, int o) {
     double x = 0.0;
-    for (int i = is[c]; i < is[c + 1]; ++i) x += slots[(size_t)i * slot + o];
+    const int end = is[c + 1];
+#pragma unroll 8
+    for (int i = is[c]; i < end; ++i) x += slots[(size_t)i * slot + o];
     return x;
 }
 
@@ -521,6 +525,7 @@ __global__ void __launch_bounds__(kWG) k_uv_sum(UvArgs a, UvSort s, SortPtrs t, 
             int at = is[cu * ncv + v0];
             for (int cv = v0; cv <= v1; ++cv) {
                 const int end = is[cu * ncv + cv + 1];
+#pragma unroll 8
                 for (; at < end; ++at) x += slots[(size_t)at * s.slot + o - 4 * cv];
             }
         }
@@ -582,8 +587,9 @@ bool uv_sort_plan(int B, int p, int q, int nu_c, int nv_c, int npts, size_t head
     s.cells = (int)cells;
     // nothing that fixes the order of a sum depends on B, so that a surface's
     // result does not depend on the batch it is in
+    // 64 chunks of 256 to 2048 pairs, more chunks beyond
     const long long c = ((long long)npts + 63) / 64;
-    s.chunk = (int)std::max<long long>(256, (c + kWave - 1) / kWave * kWave);
+    s.chunk = (int)std::min<long long>(2048, std::max<long long>(256, (c + kWave - 1) / kWave * kWave));
     s.nchunk = (npts + s.chunk - 1) / s.chunk;
     s.seg = npts >= 32768 ? 512 : 128;
     s.items = (int)(std::min<long long>(cells, npts) + npts / s.seg);
@@ -626,7 +632,8 @@ hipError_t launch_uv_bwd_sorted(const UvArgs& a, const UvSort& s, char* ws, hipS
     for (int b0 = 0; b0 < a.B; b0 += s.group) {
         const unsigned nb = (unsigned)std::min(s.group, a.B - b0);
         hipLaunchKernelGGL(k_uv_hist, dim3((unsigned)s.nchunk, nb), dim3(kWG), lds, st, a, s, t, b0);
-        hipLaunchKernelGGL(k_uv_scan, dim3(nb), dim3(kScanWG), 0, st, s, t);
+        if (s.cells <= kScanPer * kWG) hipLaunchKernelGGL(k_uv_scan<kWG>, dim3(nb), dim3(kWG), 0, st, s, t);
+        else hipLaunchKernelGGL(k_uv_scan<kUvCellsMax / kScanPer>, dim3(nb), dim3(kUvCellsMax / kScanPer), 0, st, s, t);
         hipLaunchKernelGGL(k_uv_order, dim3((unsigned)s.nchunk, nb), dim3(kWave), lds, st, a, s, t, bits);
         const dim3 gi((unsigned)((s.items + kWavesPerWG - 1) / kWavesPerWG), nb);
         const int m = std::max(a.p, a.q);
