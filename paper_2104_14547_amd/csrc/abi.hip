@@ -272,14 +272,6 @@ struct UniformGeom {
     int group;          // surfaces the backward takes at a time (its workspace holds their slots)
 };
 
-// Most workspace the backward's slots take unless one surface needs more.
-constexpr size_t kGroupBytes = size_t(1) << 30;
-
-// Workspace for B surfaces of `one` bytes taken in groups.  In bytes, not in
-// whole surfaces, so that it grows with both and a workspace sized for a
-// larger call serves a smaller one.
-size_t group_ws(size_t B, size_t one) { return std::max(one, std::min(B * one, kGroupBytes)); }
-
 // Rows of a forward tile when the caller set none.  A point's bits do not
 // depend on the tile it is in, so the rows may follow the batch: enough tiles
 // to give every SIMD four waves, 8 to 64 rows
@@ -851,9 +843,7 @@ int nurbs_surface_uv_ws_bytes(nurbs_ctx* ctx, int B, int p, int q, int nu_c, int
     if (grad_mask & ~NURBS_GRAD_ALL) return fail(ctx, NURBS_EINVAL, "unknown gradient bits");
     if (grad_mask == 0) *out = (ctx->flags & NURBS_VALIDATE) ? kWsHeader : 0;
     else {
-        *out = uv_layout(B, p, q, nu_c, nv_c).total;
-        UvSort so;
-        if (uv_sort_plan(B, p, q, nu_c, nv_c, npts, kWsHeader, &so)) *out = std::max(*out, so.total);
+        *out = std::max(uv_layout(B, p, q, nu_c, nv_c).total, uv_sort_asked(B, p, q, nu_c, nv_c, npts, kWsHeader));
     }
     return NURBS_OK;
 }

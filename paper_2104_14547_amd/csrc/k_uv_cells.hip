@@ -564,6 +564,19 @@ void launch_cell(dim3 grid, hipStream_t st, const UvArgs& a, const UvSort& s, co
 
 }  // namespace
 
+namespace {
+constexpr int kLongItems = 32768;  // pairs from which items are longer
+
+size_t al256(size_t x) { return (x + 255) & ~size_t(255); }
+int sort_slot(int p, int q) { return 4 * (p + 1) * (q + 1) + 2 * p + 2 * q; }
+
+// Tables and slots of one surface; those of G take at most G times as much.
+size_t sort_bytes(size_t cells, size_t chunks, size_t items, size_t slot, size_t npts) {
+    return al256(4 * chunks * cells) + 2 * al256(4 * (cells + 1)) + al256(4 * items) + al256(4 * npts) +
+           al256(2 * npts) + al256(8 * items * slot);
+}
+}  // namespace
+
 bool uv_sort_plan(int B, int p, int q, int nu_c, int nv_c, int npts, size_t head, UvSort* out) {
     UvSort s{};
     s.ncv = nv_c - q;
@@ -591,25 +604,33 @@ bool uv_sort_plan(int B, int p, int q, int nu_c, int nv_c, int npts, size_t head
     const long long c = ((long long)npts + 63) / 64;
     s.chunk = (int)std::min<long long>(2048, std::max<long long>(256, (c + kWave - 1) / kWave * kWave));
     s.nchunk = (npts + s.chunk - 1) / s.chunk;
-    s.seg = npts >= 32768 ? 512 : 128;
+    s.seg = npts >= kLongItems ? 512 : 128;
     s.items = (int)(std::min<long long>(cells, npts) + npts / s.seg);
-    s.slot = 4 * (p + 1) * (q + 1) + 2 * p + 2 * q;
-    auto al = [](size_t x) { return (x + 255) & ~size_t(255); };
-    // at most 1 GiB of tables and slots at a time
-    size_t one = al(4 * (size_t)s.nchunk * s.cells) + 2 * al(4 * (size_t)(s.cells + 1)) + al(4 * (size_t)s.items) +
-                 al(6 * (size_t)npts) + al(8 * (size_t)s.items * s.slot);
-    s.group = (int)std::max<long long>(1, std::min<long long>(B, (long long)((size_t(1) << 30) / one)));
+    s.slot = sort_slot(p, q);
+    const size_t one = sort_bytes(s.cells, s.nchunk, s.items, s.slot, npts);
+    s.total = head + group_ws(B, one);
+    s.group = (int)std::min<size_t>(B, (s.total - head) / one);
     const size_t G = (size_t)s.group;
     s.hist = head;
-    s.cell_start = s.hist + al(4 * G * s.nchunk * s.cells);
-    s.item_start = s.cell_start + al(4 * G * (s.cells + 1));
-    s.item_cell = s.item_start + al(4 * G * (s.cells + 1));
-    s.order = s.item_cell + al(4 * G * s.items);
-    s.cell_of = s.order + al(4 * G * npts);
-    s.slots = s.cell_of + al(2 * G * npts);
-    s.total = s.slots + al(8 * G * s.items * s.slot);
+    s.cell_start = s.hist + al256(4 * G * s.nchunk * s.cells);
+    s.item_start = s.cell_start + al256(4 * G * (s.cells + 1));
+    s.item_cell = s.item_start + al256(4 * G * (s.cells + 1));
+    s.order = s.item_cell + al256(4 * G * s.items);
+    s.cell_of = s.order + al256(4 * G * npts);
+    s.slots = s.cell_of + al256(2 * G * npts);
     *out = s;
     return true;
+}
+
+size_t uv_sort_asked(int B, int p, int q, int nu_c, int nv_c, int npts, size_t head) {
+    if (npts < 1) return 0;
+    // a lower degree on the same net has more cells, fewer pairs may take more
+    // and shorter items and more chunks
+    const size_t cells = std::min<size_t>(kUvCellsMax, (size_t)(nu_c - 1) * (nv_c - 1)), n = (size_t)npts;
+    const size_t chunks = std::max(std::min<size_t>(64, (n + 255) / 256), (n + 2047) / 2048);
+    const size_t items = std::min(cells, n) +
+                         (npts < kLongItems ? n / 128 : std::max<size_t>(n / 512, (kLongItems - 1) / 128));
+    return head + group_ws(B, sort_bytes(cells, chunks, items, sort_slot(p, q), n));
 }
 
 hipError_t launch_uv_bwd_sorted(const UvArgs& a, const UvSort& s, char* ws, hipStream_t st, const float* gpts,

@@ -136,6 +136,18 @@ struct UvArgs {
     int* err;     // device error word (NURBS_VALIDATE) or NULL
 };
 
+// Most workspace that a batch's tables and slots take unless one surface needs
+// more: the backwards take a batch in groups of surfaces.
+constexpr size_t kGroupBytes = size_t(1) << 30;
+
+// Workspace for B surfaces of `one` bytes taken in groups.  In bytes, not in
+// whole surfaces, so that it grows with both and a workspace sized for a
+// larger call serves a smaller one.
+inline size_t group_ws(size_t B, size_t one) {
+    const size_t all = B * one < kGroupBytes ? B * one : kGroupBytes;
+    return all > one ? all : one;
+}
+
 // Scattered backward over pairs ordered by cell (k_uv_cells.hip): the sizes
 // for one surface shape and the byte offsets in the workspace of a group of
 // `group` surfaces (the batch is taken a group at a time).
@@ -150,6 +162,9 @@ struct UvSort {
     size_t hist, cell_start, item_start, item_cell, order, cell_of, slots, total;
 };
 bool uv_sort_plan(int B, int p, int q, int nu_c, int nv_c, int npts, size_t head, UvSort* out);
+// Bytes to ask for: no less for a call that is larger in any of its sizes, and
+// enough for every smaller one, whichever path it takes.
+size_t uv_sort_asked(int B, int p, int q, int nu_c, int nv_c, int npts, size_t head);
 hipError_t launch_uv_bwd_sorted(const UvArgs& a, const UvSort& s, char* ws, hipStream_t st, const float* gpts,
                                 unsigned mask, float* gc, float* gw, float* gku, float* gkv);
 constexpr int kUvLdsAccMax = 7424;                 // accumulators a workgroup keeps in LDS (58 KiB)
