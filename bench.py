@@ -701,7 +701,7 @@ def main():
     achieved = ab[dom] / (avg[dom] * 1e-3) / 1e9
     kernels = {names[k]: {"avg_ms": avg[k], "algorithmic_bytes": ab[k],
                           "achieved_GBs": ab[k] / (avg[k] * 1e-3) / 1e9} for k in avg}
-    chosen = tune["chosen"] if tune else {"schedule": "static", "fwd_tile_points": 16384, "bwd_tile_points": 16384}
+    chosen = tune["chosen"] if tune else {"schedule": "static", "fwd_tile_points": 0, "bwd_tile_points": 0}
     traffic = traffic_for(names[dom], args.workload, chosen)
 
     result = {

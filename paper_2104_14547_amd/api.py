@@ -62,6 +62,7 @@ class Context:
         _check(N.lib().nurbs_ctx_create(self.device, ctypes.byref(h)))
         self.handle = h
         self.flags = 0
+        self.tiling = (0, 0)
         if validate:
             self.set_flags(N.NURBS_VALIDATE)
 
@@ -82,13 +83,14 @@ class Context:
         _check(N.lib().nurbs_ctx_set_knot_sigma(self.handle, float(sigma)), self.handle)
 
     def set_tiling(self, fwd_tile_points: int = 0, bwd_tile_points: int = 0):
-        """Target sample points per forward / backward tile of later calls (0: default)."""
+        """Target sample points per forward / backward tile of later calls (0:
+        the library's default rule, which is no number of points)."""
         _check(N.lib().nurbs_ctx_set_tiling(self.handle, int(fwd_tile_points), int(bwd_tile_points)), self.handle)
-        self.tiling = (int(fwd_tile_points) or 16384, int(bwd_tile_points) or 16384)
+        self.tiling = (int(fwd_tile_points), int(bwd_tile_points))
 
     def set_schedule(self, schedule: int):
         """Tile schedule of plans created later on this context
-        (NURBS_SCHED_DYNAMIC, the default, or NURBS_SCHED_STATIC)."""
+        (NURBS_SCHED_STATIC, the default, or NURBS_SCHED_DYNAMIC)."""
         _check(N.lib().nurbs_ctx_set_schedule(self.handle, int(schedule)), self.handle)
         self.schedule = int(schedule)
 

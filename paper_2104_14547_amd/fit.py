@@ -21,8 +21,9 @@ with a precomputed basis) and every step reads them
 The fit owns a library context whose tiling (sample points per forward and
 backward tile) is chosen at construction by timing the candidates on the
 problem itself (``tiling="auto"``): the library's default backward tiles (about
-72 rows, the same for every batch) are longer than is best for one surface.  The summation order, and so the bits of the result, depend on
-the tiling only.
+72 rows, the same for every batch) are longer than is best for one surface.
+The summation order, and so the bits of the result, depend on the tiling only;
+``tiling`` names the one in use, 0 being the library's default rule.
 
 With ``graph=True`` the whole step (both library launches, the loss gradient,
 Adam and the projections) is captured once in a HIP graph and replayed, so a
@@ -94,7 +95,7 @@ class SurfaceFit:
             tiling = self._tune_tiling()
         if tiling:
             self.ctx.set_tiling(*tiling)
-        self.tiling = getattr(self.ctx, "tiling", (16384, 16384))
+        self.tiling = self.ctx.tiling
         for t in params:
             t.grad = torch.zeros_like(t)
         # capturable in both modes, so eager and graph steps run the same arithmetic
