@@ -770,7 +770,7 @@ def basis(knots, p: int, x):
 # tile autotuning
 # --------------------------------------------------------------------------
 
-TILE_CANDIDATES = (2048, 4096, 8192, 16384, 65536)
+TILE_CANDIDATES = (0, 2048, 4096, 8192, 16384, 65536)  # 0: the library's default rule
 SCHEDULES = (N.NURBS_SCHED_DYNAMIC, N.NURBS_SCHED_STATIC)
 
 

@@ -36,9 +36,10 @@ import torch
 from . import _native as N
 from .api import Context, basis_table, surface_bwd, surface_bwd_tab, surface_fwd, surface_fwd_tab
 
-# points per tile tried by the tiling search: a single surface needs small
-# tiles to occupy the chip, a large one amortises the per-tile set-up
-FIT_TILE_CANDIDATES = (256, 512, 1024, 2048, 4096, 16384)
+# points per tile tried by the tiling search (0: the library's default rule): a
+# single surface needs small tiles to occupy the chip, a large one amortises
+# the per-tile set-up
+FIT_TILE_CANDIDATES = (0, 256, 512, 1024, 2048, 4096, 16384)
 
 
 def project_knots(inner, ramp, top: float):

@@ -5,7 +5,7 @@ import pytest
 torch = pytest.importorskip("torch")
 
 import paper_2104_14547_amd as nd  # noqa: E402
-from tests.test_gpu_fit import make_fit, small_problem  # noqa: E402
+from tests.test_gpu_fit import T, make_fit, small_problem  # noqa: E402
 from tests.test_gpu_tiles import batch_of  # noqa: E402
 from tests.test_zz_no_alloc import uniform_inputs  # noqa: E402
 
@@ -34,3 +34,14 @@ def test_fit_reports_what_runs():
         f.step(3)
     assert a.tiling == b.tiling == (0, 0)
     assert all(torch.equal(u, v) for u, v in zip(a.params, b.params))
+
+
+def test_tuners_may_keep_the_default():
+    assert 0 in nd.api.TILE_CANDIDATES and 0 in nd.fit.FIT_TILE_CANDIDATES
+    b = batch_of(3, 2, 3, 14, 9, 300, 90, seed=2)
+    args = [T(getattr(b, k)) for k in ("ctrl", "w", "ku", "kv", "us", "vs")]
+    plan, report = nd.api.autotune(b.shapes, b.offsets, args, T(b.upstream), candidates=(0,), reps=2)
+    assert report["chosen"]["fwd_tile_points"] == report["chosen"]["bwd_tile_points"] == 0
+    for x, y in zip(plan.backward(*args, T(b.upstream)),
+                    nd.SurfaceBatch(b.shapes, b.offsets).backward(*args, T(b.upstream))):
+        assert torch.equal(x, y)
