@@ -136,18 +136,19 @@ constexpr size_t kNoAllocScratchBytes = size_t(64) << 20;  // the built-in scrat
 // (parts of 64 rows and a remainder: 469, 172, 135, 102).  The backward of one
 // bicubic 512 x 512 surface: 49 at 64 rows, 134 at 256.
 //
-// Grids of up to kNarrow columns leave most of a wave's lanes idle and move few
-// points per slot, so their tiles are longer: 4096 bicubic surfaces of 256 x 3
-// samples on 10 x 10 nets 285 us a backward at 64 rows, 261 at 128 and at 256;
-// 1024 of degree 5 with 256 x 8 on 40 x 40 195, 175, 222; 64 of 4096 x 8 on 48 x
-// 48 135, 135, 173; one of those 85, 111, 162 (1606 at 4096 rows).
+// Grids of up to kNarrow columns move few points per slot, so their tiles are
+// longer: 4096 bicubic surfaces of 256 x 3 samples on 10 x 10 nets 285 us a
+// backward at 64 rows, 261 at 128 and at 256.  With more columns 72 rows lose
+// nothing to longer tiles on a full chip (64 of 4096 x 8 on 48 x 48: 135 us at
+// 64 and at 128 rows, 173 at 256), and short ones gain elsewhere (one of those:
+// 85, 111, 162).
 //
 // Every tile has a slot that holds a whole net, so the slots of a surface have
 // a budget: kSlotShare times its points' bytes and a MiB, at most the built-in
 // scratch, or what tiles of 16384 points take where that is more.  A surface
 // whose parts exceed it takes fewer and longer ones (one of 100000 x 1 samples
 // on a 16 x 16 net: 20 MB of slots instead of 30).
-constexpr int kDefaultRows = 72, kNarrowRows = 128, kNarrow = 8;
+constexpr int kDefaultRows = 72, kNarrowRows = 128, kNarrow = 4;
 constexpr size_t kSlotShare = 16;
 
 size_t slots_share(int nu_s, int nv_s) {
