@@ -137,7 +137,7 @@ constexpr size_t kNoAllocScratchBytes = size_t(64) << 20;  // the built-in scrat
 // bicubic 512 x 512 surface: 49 at 64 rows, 134 at 256.
 //
 // Grids of up to kNarrow columns move few points per slot, so their tiles are
-// longer: 4096 bicubic surfaces of 256 x 3 samples on 10 x 10 nets 285 us a
+// longer, up to kNarrowRows: 4096 bicubic surfaces of 256 x 3 samples on 10 x 10 nets 285 us a
 // backward at 64 rows, 261 at 128 and at 256.  With more columns 72 rows lose
 // nothing to longer tiles on a full chip (64 of 4096 x 8 on 48 x 48: 135 us at
 // 64 and at 128 rows, 173 at 256), and short ones gain elsewhere (one of those:
@@ -151,6 +151,11 @@ constexpr size_t kNoAllocScratchBytes = size_t(64) << 20;  // the built-in scrat
 constexpr int kDefaultRows = 72, kNarrowRows = 128, kNarrow = 4;
 constexpr size_t kSlotShare = 16;
 
+int default_parts(int nu_s, int nv_s) {
+    if (nv_s <= kNarrow) return (int)(((long long)nu_s + kNarrowRows - 1) / kNarrowRows);
+    return std::max(1, (int)(((long long)nu_s + kDefaultRows / 2) / kDefaultRows));
+}
+
 size_t slots_share(int nu_s, int nv_s) {
     return kSlotShare * 3 * sizeof(float) * nu_s * nv_s + (size_t(1) << 20);
 }
@@ -159,8 +164,7 @@ int default_rows(int p, int q, int nu_c, int nv_c, int nu_s, int nv_s) {
     if (nu_s < 1) return 1;
     auto parts_of = [&](int n) { return (nu_s + n - 1) / n; };
     auto bytes = [&](int rows) { return slots_bytes(p, q, nu_c, nv_c, nu_s, nv_s, rows); };
-    const int aim = nv_s <= kNarrow ? kNarrowRows : kDefaultRows;
-    int rows = parts_of(std::max(1, (int)(((long long)nu_s + aim / 2) / aim)));
+    int rows = parts_of(default_parts(nu_s, nv_s));
     const int coarse = tile_rows(nu_s, nv_s, kDefaultTilePts);
     const size_t budget =
         std::max(bytes(coarse), std::min(kNoAllocScratchBytes - kWsHeader, slots_share(nu_s, nv_s)));
@@ -308,10 +312,9 @@ UniformGeom uniform_geom(const nurbs_ctx* c, int B, int p, int q, int nu_c, int 
 size_t slots_asked(const nurbs_ctx* c, const UniformGeom& g, int p, int q, int nu_c, int nv_c, int nu_s, int nv_s) {
     if (c->bwd_tile_pts || nu_s < 1) return g.one;
     const size_t tile = slot_bytes(p, q, nu_c, nv_c, 0) + 16, row = sizeof(float) * (size_t)(p + 1);
-    const int aim = nv_s <= kNarrow ? kNarrowRows : kDefaultRows, coarse = tile_rows(nu_s, nv_s, kDefaultTilePts);
-    // parts of fewer than 2 kNarrowRows rows; the last tile's are counted whole
-    const size_t fine = g.ncb * (tile * std::max<size_t>(1, ((size_t)nu_s + aim / 2) / aim) +
-                                 row * ((size_t)nu_s + 2 * kNarrowRows));
+    const int coarse = tile_rows(nu_s, nv_s, kDefaultTilePts);
+    // parts of at most kNarrowRows rows; the last tile's are counted whole
+    const size_t fine = g.ncb * (tile * default_parts(nu_s, nv_s) + row * ((size_t)nu_s + kNarrowRows));
     const size_t most = g.ncb * (tile * (((size_t)nu_s + coarse - 1) / coarse) + row * 2 * nu_s);
     return std::max(most, std::min(fine, std::min(kNoAllocScratchBytes - kWsHeader, slots_share(nu_s, nv_s))));
 }
