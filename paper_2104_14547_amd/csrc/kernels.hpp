@@ -1247,6 +1247,12 @@ __device__ __forceinline__ void knot_gradient(const float* __restrict__ Ug, int 
 constexpr int kFinChunk = kWave * kFinCp;  // control points per dP/dW part of a plan
 constexpr int kFinKU = 0, kFinKV = 1, kFinPW = 2;
 
+// One rounding order whatever CP and FLY: left to itself the compiler fuses
+// either product of a sum of two, and the choice differs between instances.
+__device__ __forceinline__ float dot3(float a, float x, float b, float y, float c, float z) {
+    return __builtin_fmaf(c, z, __builtin_fmaf(b, y, a * x));
+}
+
 // Sum of the tile rectangles over CP * 64 control points from base on, CP per
 // lane, in tile order, FLY tiles' loads in flight at a time.  The lanes look
 // at 64 tiles' headers at once; only tiles whose rectangle meets the chunk's
@@ -1304,7 +1310,7 @@ __device__ __forceinline__ void fin_pw_chunk(const Surf& s, int ntiles, TileAt t
                     acc[c].x += x.x;
                     acc[c].y += x.y;
                     acc[c].z += x.z;
-                    acc[c].w += x.w - (ct[f].x * x.x + ct[f].y * x.y + ct[f].z * x.z);
+                    acc[c].w += x.w - dot3(ct[f].x, x.x, ct[f].y, x.y, ct[f].z, x.z);
                 }
         }
     }
@@ -1319,7 +1325,7 @@ __device__ __forceinline__ void fin_pw_chunk(const Surf& s, int ntiles, TileAt t
             gctrl[3 * ij + 1] = wt * acc[c].y;
             gctrl[3 * ij + 2] = wt * acc[c].z;
         }
-        if (mask & 2u) gw[ij] = pc[0] * acc[c].x + pc[1] * acc[c].y + pc[2] * acc[c].z + acc[c].w;
+        if (mask & 2u) gw[ij] = dot3(pc[0], acc[c].x, pc[1], acc[c].y, pc[2], acc[c].z) + acc[c].w;
     }
 }
 
