@@ -15,13 +15,15 @@
 // (Sec. 3.2.1).  dL/dw is taken directly from P_i - C (not as P . dL/dPw +
 // dL/dPw_w), so no difference of two large sums is formed.
 //
-// Work decomposition.  A workgroup (4 waves, 1 to 4 in the backward) owns one chunk
-// of up to kCurveChunk consecutive samples of one curve and stages that
-// curve's knots and control polygon in LDS.  Forward: one sample per lane.  Backward: the
-// chunk's samples are put in span order (sorted parameters, the usual case,
-// are in it already; others go through a stable counting sort in LDS) and the
-// samples of a span are cut into items, one item per lane at a time.  Lanes of one span form runs; a DPP segmented scan (the surface
-// backward's, one v_fmac_f32_dpp per value and step) sums each run, whose last
+// Work decomposition.  A workgroup (4 waves, 1 to 4 in the backward) owns one
+// chunk of up to kCurveChunk consecutive samples of one curve and stages that
+// curve's knots and control polygon in LDS.  Forward: one sample per lane.
+// Backward: the chunk's samples are put in span order (sorted parameters, the
+// usual case, are in it already; others go through a stable counting sort in
+// LDS) and the samples of a span are cut into items, one item per lane at a
+// time; sorted samples with few to a span go one to a lane as they are.  Lanes
+// of one span form runs; a DPP segmented scan (the surface backward's, one
+// v_fmac_f32_dpp per value and step) sums each run, whose last
 // lane adds the sums into the wave's LDS accumulators, without atomics.  At
 // the end of the chunk the waves' accumulators are added in wave order.
 // A curve with one chunk writes its gradients directly; longer curves write
@@ -165,12 +167,26 @@ __global__ void __launch_bounds__(kWG) k_curve_fwd(CurveArgs a, float* __restric
 // backward
 // --------------------------------------------------------------------------
 
-// Waves of a backward workgroup, by the samples of its chunk: enough that a
-// lane's item holds several samples, few enough that a pass over the items
-// fills every wave (four waves for a thousand samples left one of them idle:
-// 227 us against 155 us), and with one wave the workgroup's barriers cost
-// nothing.
-constexpr int curve_waves(int chunk) { return chunk <= 384 ? 1 : chunk <= 1024 ? 2 : 4; }
+// Sorted samples of a chunk that has few to a span are taken as they come, one
+// to a lane, as items would hold one or two of them: no span order, no items.
+// 16384 cubic curves of 64 control points x 64 samples 34 us (42 in items, 62
+// with the kernel before items), 2048 of 240 x 512 31 (37; 27).
+__host__ __device__ inline bool curve_direct(int chunk, int spans) { return chunk <= 4 * spans; }
+
+// Waves of a backward workgroup, by the samples of its chunk and the spans (the
+// batch must not decide: the waves fix the order of the sums).  Samples taken
+// as they come: a pass or two over them.  Items: enough waves that a lane's
+// item holds several samples, few enough that a pass over the items fills
+// every one, and with one wave the workgroup's barriers cost nothing (16384
+// cubic curves of 32 control points x 384 samples: 62 us with one wave, 89 with
+// two, 146 with four; x 1024: 123 with two, 179 with four; 64 curves x 256: 12,
+// 11, 10.5).  Long polygons fill four with fewer samples (2048 of 240 x 1024: 42
+// us, 57 with two).
+inline int curve_waves(int chunk, int spans) {
+    if (curve_direct(chunk, spans)) return chunk <= kWave ? 1 : chunk <= 2 * kWave ? 2 : 4;
+    if (spans >= 128 && chunk <= 8 * spans) return 4;
+    return chunk <= 384 ? 1 : chunk <= 1024 ? 2 : 4;
+}
 
 // The workgroup's LDS (dynamic, sized by the curve's control points).
 struct CurveLds {
@@ -243,20 +259,27 @@ __device__ __forceinline__ int span_prefix(const CurveLds& l, int spans, int* ou
     return all;
 }
 
-// Put the chunk's n samples (l.us) in span order: l.first, and l.perm when the
-// parameters are not sorted (returns whether they are).  The order within a
-// span is the input's.
+// Whether the chunk's n parameters (l.us) are sorted.
 template <int W>
-__device__ __forceinline__ bool curve_order(const CurveLds& l, int p, int nc, int n) {
+__device__ __forceinline__ bool curve_sorted(const CurveLds& l, int p, int nc, int n) {
     constexpr int kT = W * kWave;
-    const int t = threadIdx.x, spans = nc - p, wv = t / kWave, lane = lane_id();
+    const int t = threadIdx.x, spans = nc - p;
     bool bad = false;
     for (int s = t + 1; s < n; s += kT) bad |= !(l.us[s - 1] <= l.us[s]);
     // knots out of order (only flagged, under NURBS_VALIDATE) go by find_span,
     // which stays in range whatever they are
     for (int c = t; c < spans; c += kT) bad |= !(l.U[p + c] <= l.U[p + c + 1]);
     if (t == 0) bad |= !(l.U[nc - 1] < l.U[nc]);
-    if (!__syncthreads_or(bad)) {
+    return !__syncthreads_or(bad);
+}
+
+// Put the chunk's n samples (l.us) in span order: l.first, and l.perm when the
+// parameters are not sorted.  The order within a span is the input's.
+template <int W>
+__device__ __forceinline__ void curve_order(const CurveLds& l, int p, int nc, int n, bool sorted) {
+    constexpr int kT = W * kWave;
+    const int t = threadIdx.x, spans = nc - p, wv = t / kWave, lane = lane_id();
+    if (sorted) {
         // sorted: a span starts at the first sample not below its knot, one
         // search per knot instead of one per sample; an empty span starts
         // where the next one does
@@ -270,7 +293,7 @@ __device__ __forceinline__ bool curve_order(const CurveLds& l, int p, int nc, in
             l.first[c] = lo;
         }
         __syncthreads();
-        return true;
+        return;
     }
     // stable counting sort: each wave takes its part of the samples
     auto span_of = [&](int s) { return find_span(l.U, p, nc - 1, l.us[s]) - p; };
@@ -315,32 +338,34 @@ __device__ __forceinline__ bool curve_order(const CurveLds& l, int p, int nc, in
         if (act) l.perm[base + rank] = (unsigned short)(s + lane);
     }
     __syncthreads();
-    return false;
 }
 
-// Cut the spans into items of at most the returned number of samples; l.item.
+// Cut the spans into items of samples, l.item; returns their number.
 // A lane's samples share their span, so the span's knots, reciprocals and
 // control points are read once for all of them and the sums over them stay in
 // registers; the scan over the wave and the LDS adds come once per 64 items.
 // The length is the least that fills the waves once (a multiple of that for
 // curves of many spans): an item more than the lanes would cost a whole pass.
+// The room is more than twice the spans used, so that the second length is
+// about a span's average and not all of its samples.
 template <int W>
-__device__ __forceinline__ int curve_items(const CurveLds& l, int spans, int n, int* nitems) {
+__device__ __forceinline__ int curve_items(const CurveLds& l, int spans, int n) {
     constexpr int kT = W * kWave;
     int used = 0;
     for (int c0 = 0; c0 < spans; c0 += kT) {
         const int c = c0 + (int)threadIdx.x;
         used += __syncthreads_count(c < spans && l.first[c + 1] > l.first[c]);
     }
-    const int room = kT * (used / kWave + 1);  // more than the spans used, so both lengths exist
-    int len = (2 * n + 2 * room - used - 1) / (2 * room - used);  // half an item lost per span
+    const int room = kT * ((2 * used + kT) / kT);  // more than twice the spans used
+    // half an item lost per span, none with one sample to an item
+    int len = n <= room ? 1 : (2 * n + 2 * room - used - 1) / (2 * room - used);
     auto count = [&](int c) { return (l.first[c + 1] - l.first[c] + len - 1) / len; };
-    *nitems = span_prefix<W>(l, spans, l.item, count);
-    if (*nitems > room) {
+    int nitems = span_prefix<W>(l, spans, l.item, count);
+    if (nitems > room) {
         len = (n + room - used - 1) / (room - used);  // a whole one: fits
-        *nitems = span_prefix<W>(l, spans, l.item, count);
+        nitems = span_prefix<W>(l, spans, l.item, count);
     }
-    return len;
+    return nitems;
 }
 
 // One sample's parameter (from LDS) and dL/dC.
@@ -413,8 +438,10 @@ __device__ __forceinline__ void seg_scan_select(float4 (&c)[P1], float (&g)[K], 
 // 64 control points, 4096 x 4096 samples 285 us a pass against 160); dL/dC
 // staged in LDS: 189 us (fewer workgroups resident).  Parameters in random
 // order (4096 quartic curves x 1000 samples): 847 -> 112 us a pass.
+// Degree 5 is held to three waves per SIMD (168 registers, no spills; 181 and two
+// waves otherwise): 16384 curves of 32 control points x 1024 samples 262 -> 218 us.
 template <int P, int DIM, int W>
-__global__ void __launch_bounds__(W* kWave) k_curve_bwd(CurveArgs a, const float* __restrict__ gpts,
+__global__ void __launch_bounds__(W* kWave, P == 5 ? 3 : 1) k_curve_bwd(CurveArgs a, const float* __restrict__ gpts,
                                                         float* __restrict__ gctrl, float* __restrict__ gw,
                                                         float* __restrict__ gk, float* __restrict__ part,
                                                         unsigned mask) {
@@ -425,17 +452,21 @@ __global__ void __launch_bounds__(W* kWave) k_curve_bwd(CurveArgs a, const float
     const CurveLds l = curve_lds<W>(reinterpret_cast<char*>(curve_dyn), a.nc, P, min(a.ns, kCurveChunk));
     const float* us = a.us + (a.u_shared ? 0 : (size_t)b.c * a.ns);
     stage_curve<DIM>(a, P, b.c, l.U, l.pw);
-    for (int i = threadIdx.x; i < n; i += kT) l.us[i] = us[b.s0 + i];
+    const float* kn = a.knots + (size_t)b.c * nU;
+    const float ulo = kn[P], uhi = kn[a.nc];
+    for (int i = threadIdx.x; i < n; i += kT) l.us[i] = fminf(fmaxf(us[b.s0 + i], ulo), uhi);
     const float* g0 = gpts + ((size_t)b.c * a.ns + b.s0) * DIM;
     for (int i = threadIdx.x; i < W * a.nc; i += kT) l.acc[i] = make_float4(0.f, 0.f, 0.f, 0.f);
     for (int i = threadIdx.x; i < W * nU; i += kT) l.acck[i] = 0.f;
     __syncthreads();
     if (a.err) curve_validate(a, P, b.c, b.chunk, b.s0, b.s1, l.U, a.w + (size_t)b.c * a.nc, us);
-    for (int i = threadIdx.x; i < n; i += kT) l.us[i] = clamp_param(l.U, P, a.nc - 1, l.us[i]);
-    __syncthreads();
-    const bool in_order = curve_order<W>(l, P, a.nc, n);
-    int nitems;
-    const int len = curve_items<W>(l, spans, n, &nitems);
+    const bool in_order = curve_sorted<W>(l, P, a.nc, n);
+    const bool direct = in_order && curve_direct(min(a.ns, kCurveChunk), spans);
+    int nitems = n;
+    if (!direct) {
+        curve_order<W>(l, P, a.nc, n, in_order);
+        nitems = curve_items<W>(l, spans, n);
+    }
     const bool want_k = (mask & NURBS_GRAD_KU) != 0;
     const int wv = threadIdx.x / kWave;
     const int lane = lane_id();
@@ -445,16 +476,23 @@ __global__ void __launch_bounds__(W* kWave) k_curve_bwd(CurveArgs a, const float
     for (int base = wv * kWave; base < nitems; base += kT) {
         const bool act = base + lane < nitems;
         const int it = min(base + lane, nitems - 1);
-        // the item's span: the last one that starts at or before it
-        int lo = 0, hi = spans;
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (l.item[mid] <= it) lo = mid; else hi = mid;
+        // the item's span (the last one that starts at or before it), its m
+        // items and the end j1 of its samples.  The items of a span take its
+        // samples in turn, so that their lanes read neighbouring samples at
+        // each step.
+        int lo = 0, m = 1, i = it, j1 = it + 1;
+        if (direct) {
+            lo = find_span(l.U, P, a.nc - 1, l.us[it]) - P;
+        } else {
+            int hi = spans;
+            while (hi - lo > 1) {
+                const int mid = (lo + hi) >> 1;
+                if (l.item[mid] <= it) lo = mid; else hi = mid;
+            }
+            m = l.item[lo + 1] - l.item[lo];
+            i = l.first[lo] + it - l.item[lo];
+            j1 = l.first[lo + 1];
         }
-        // the m items of a span take its samples in turn, so that their lanes
-        // read neighbouring samples at each step
-        const int m = l.item[lo + 1] - l.item[lo], j1 = l.first[lo + 1];
-        int i = l.first[lo] + it - l.item[lo];
         const int k = lo + P;
         float K[2 * P], inv[P * (P + 1) / 2];
 #pragma unroll
@@ -470,11 +508,16 @@ __global__ void __launch_bounds__(W* kWave) k_curve_bwd(CurveArgs a, const float
         for (int r = 0; r <= P; ++r) c4[r] = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
         for (int t = 0; t < 2 * P; ++t) gU[t] = 0.f;
+        // steps of the wave's longest item
+        int steps = act ? (j1 - i + m - 1) / m : 0;
+#pragma unroll
+        for (int d = 1; d < kWave; d <<= 1) steps = max(steps, __shfl_xor(steps, d));
+        steps = uniform(steps);
         // one sample ahead: the loads of the next overlap the current one's work
         CurveSample<DIM> nx;
         nx.load(l.us, g0, in_order ? i : (int)l.perm[i]);
 #pragma unroll 1
-        for (int j = 0; j < len; ++j, i += m) {
+        for (int j = 0; j < steps; ++j, i += m) {
             const CurveSample<DIM> x = nx;
             const int ni = min(i + m, j1 - 1);
             nx.load(l.us, g0, in_order ? ni : (int)l.perm[ni]);
@@ -548,8 +591,8 @@ __global__ void __launch_bounds__(W* kWave) k_curve_bwd(CurveArgs a, const float
     }
     __syncthreads();
     // the chunk's totals, waves added in order
-    const bool direct = a.nchunks == 1;
-    float* pc = direct ? nullptr : part + ((size_t)b.c * a.nchunks + b.chunk) * a.part_floats;
+    const bool one = a.nchunks == 1;
+    float* pc = one ? nullptr : part + ((size_t)b.c * a.nchunks + b.chunk) * a.part_floats;
     for (int i = threadIdx.x; i < a.nc; i += kT) {
         float4 v = l.acc[i];
 #pragma unroll
@@ -560,7 +603,7 @@ __global__ void __launch_bounds__(W* kWave) k_curve_bwd(CurveArgs a, const float
             v.z += o.z;
             v.w += o.w;
         }
-        if (direct) {
+        if (one) {
             const size_t ci = (size_t)b.c * a.nc + i;
             if (mask & NURBS_GRAD_CTRL) {
                 gctrl[ci * DIM] = v.x;
@@ -577,7 +620,7 @@ __global__ void __launch_bounds__(W* kWave) k_curve_bwd(CurveArgs a, const float
             float v = l.acck[t];
 #pragma unroll
             for (int w2 = 1; w2 < W; ++w2) v += l.acck[w2 * nU + t];
-            if (direct) gk[(size_t)b.c * nU + t] = v;
+            if (one) gk[(size_t)b.c * nU + t] = v;
             else pc[4 * a.nc + t] = v;
         }
     }
@@ -638,7 +681,7 @@ void curve_bwd_kernel(const CurveArgs& a, hipStream_t st, const float* gpts, flo
 template <int P, int DIM>
 hipError_t curve_bwd_launch(const CurveArgs& a, hipStream_t st, const float* gpts, float* gctrl, float* gw,
                             float* gk, float* part, unsigned mask) {
-    const int w = curve_waves(std::min(a.ns, kCurveChunk));
+    const int w = curve_waves(std::min(a.ns, kCurveChunk), a.nc - P);
     if (w == 1) curve_bwd_kernel<P, DIM, 1>(a, st, gpts, gctrl, gw, gk, part, mask);
     else if (w == 2) curve_bwd_kernel<P, DIM, 2>(a, st, gpts, gctrl, gw, gk, part, mask);
     else curve_bwd_kernel<P, DIM, 4>(a, st, gpts, gctrl, gw, gk, part, mask);
