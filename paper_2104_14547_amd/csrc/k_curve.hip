@@ -76,44 +76,46 @@ __device__ __forceinline__ CurveBlock curve_block(const CurveArgs& a) {
     return b;
 }
 
-// Stage the curve's knots and control points (xyz or xy, and the weight) in LDS.
-template <int DIM>
+// Stage the curve's knots and control points (xyz or xy, times the weight if
+// HOM, and the weight) in LDS.
+template <int DIM, bool HOM = false>
 __device__ __forceinline__ void stage_curve(const CurveArgs& a, int p, int c, float* U, float4* Pw) {
     const int nU = a.nc + p + 1;
     const float* kn = a.knots + (size_t)c * nU;
     const float* cp = a.ctrl + (size_t)c * a.nc * DIM;
     const float* w = a.w + (size_t)c * a.nc;
     for (int i = threadIdx.x; i < nU; i += blockDim.x) U[i] = kn[i];
-    for (int i = threadIdx.x; i < a.nc; i += blockDim.x)
-        Pw[i] = make_float4(cp[i * DIM], cp[i * DIM + 1], DIM == 3 ? cp[i * DIM + 2] : 0.f, w[i]);
+    for (int i = threadIdx.x; i < a.nc; i += blockDim.x) {
+        const float wt = w[i], f = HOM ? wt : 1.f;
+        Pw[i] = make_float4(cp[i * DIM] * f, cp[i * DIM + 1] * f, DIM == 3 ? cp[i * DIM + 2] * f : 0.f, wt);
+    }
 }
 
 // --------------------------------------------------------------------------
 // forward
 // --------------------------------------------------------------------------
 // What bounds it: VALU issue.  So what samples share is formed once per
-// workgroup: the homogeneous control points and, up to degree kCurveTabDeg
-// (beyond it the table would hold a workgroup's LDS to fewer residents), the
-// reciprocals of every span's knot intervals.  16384 cubic space curves x 1024
-// samples: 53.5 us, 3.8 TB/s of points written; with both formed per sample 62
-// us, 3.9e7 wave instructions (63 us of issue).
+// workgroup: the homogeneous control points and, where a workgroup has samples
+// enough to repay it, the reciprocals of every span's knot intervals (not
+// beyond degree kCurveTabDeg, where the table would hold a workgroup's LDS to
+// fewer residents).  16384 cubic space curves x 1024 samples: 53.5 us, 3.8 TB/s
+// of points written; with both formed per sample 62 us, 3.9e7 wave instructions
+// (63 us of issue).  With and without the table, 16384 curves of 16 control
+// points: degree 1, 16 samples 13.4 and 12.7 us; 3, 256 25.5 and 25.6; 3, 1024
+// 57 and 59; 4, 256 27.5 and 30.8; 4, 64 17.3 and 14.9.
 constexpr int kCurveTabDeg = 4;
+inline bool curve_tab(int p, int ns) { return p >= 2 && ns >= (p >= 4 ? 256 : 512); }
 
-template <int P, int DIM, bool DU>
+template <int P, int DIM, bool DU, bool kTab>
 __global__ void __launch_bounds__(kWG) k_curve_fwd(CurveArgs a, float* __restrict__ pts, float* __restrict__ du) {
-    constexpr bool kTab = !DU && P <= kCurveTabDeg;
     constexpr int kInv = P * (P + 1) / 2;
     __shared__ float U[kWG];
     __shared__ float4 Pw[kWG];
     __shared__ float tab[kTab ? kWG * kInv : 1];
     const CurveBlock b = curve_block(a);
-    stage_curve<DIM>(a, P, b.c, U, Pw);
+    stage_curve<DIM, true>(a, P, b.c, U, Pw);
     __syncthreads();
-    for (int i = threadIdx.x; i < a.nc; i += kWG) {
-        const float4 q = Pw[i];
-        Pw[i] = make_float4(q.x * q.w, q.y * q.w, q.z * q.w, q.w);
-    }
-    if constexpr (kTab)
+    if constexpr (kTab) {
         for (int i = threadIdx.x; i < a.nc - P; i += kWG) {
             float K[2 * P], inv[kInv];
 #pragma unroll
@@ -122,7 +124,8 @@ __global__ void __launch_bounds__(kWG) k_curve_fwd(CurveArgs a, float* __restric
 #pragma unroll
             for (int t = 0; t < kInv; ++t) tab[i * kInv + t] = inv[t];
         }
-    __syncthreads();
+        __syncthreads();
+    }
     const float* us = a.us + (a.u_shared ? 0 : (size_t)b.c * a.ns);
     if (a.err) curve_validate(a, P, b.c, b.chunk, b.s0, b.s1, U, a.w + (size_t)b.c * a.nc, us);
     const size_t base = (size_t)b.c * a.ns;
@@ -665,8 +668,11 @@ __global__ void __launch_bounds__(kWG) k_curve_fin(CurveArgs a, int p, const flo
 template <int P, int DIM>
 hipError_t curve_fwd_launch(const CurveArgs& a, hipStream_t st, float* pts, float* du) {
     const dim3 grid((unsigned)((long long)a.B * a.nchunks));
-    if (du) hipLaunchKernelGGL((k_curve_fwd<P, DIM, true>), grid, dim3(kWG), 0, st, a, pts, du);
-    else hipLaunchKernelGGL((k_curve_fwd<P, DIM, false>), grid, dim3(kWG), 0, st, a, pts, du);
+    constexpr bool kMayTab = P <= kCurveTabDeg;
+    if (du) hipLaunchKernelGGL((k_curve_fwd<P, DIM, true, false>), grid, dim3(kWG), 0, st, a, pts, du);
+    else if (kMayTab && curve_tab(P, a.ns))
+        hipLaunchKernelGGL((k_curve_fwd<P, DIM, false, kMayTab>), grid, dim3(kWG), 0, st, a, pts, du);
+    else hipLaunchKernelGGL((k_curve_fwd<P, DIM, false, false>), grid, dim3(kWG), 0, st, a, pts, du);
     return hipGetLastError();
 }
 

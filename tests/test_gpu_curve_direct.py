@@ -1,7 +1,8 @@
-"""Curve backward where its split changes: samples taken as they come (at most
-four to a span, sorted) or in items, one, two or four waves, and as many spans
-in use as a workgroup has lanes, so that items have to be shared out; sorted and
-unsorted.  Bars as for the other curve tests, and the same bits in any batch."""
+"""Curves where their split changes: samples taken as they come (at most four to
+a span, sorted) or in items, one, two or four waves, as many spans in use as a
+workgroup has lanes, so that items have to be shared out, and the forward with
+and without its table; sorted and unsorted.  Bars as for the other curve tests,
+and the same bits in any batch."""
 import numpy as np
 import pytest
 
@@ -17,7 +18,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("shuffle", [False, True])
 @pytest.mark.parametrize("p,nc,ns,dim", [
     (3, 67, 64, 3), (3, 67, 65, 2), (3, 67, 128, 3), (3, 67, 129, 3), (3, 67, 256, 3), (3, 67, 257, 3), (5, 69, 256, 2),
-    (1, 64, 300, 2), (2, 66, 384, 3), (3, 240, 1024, 3), (1, 240, 1912, 2), (1, 240, 1913, 2), (7, 200, 2500, 3)])
+    (1, 64, 300, 2), (2, 66, 384, 3), (3, 240, 1024, 3), (1, 240, 1912, 2), (1, 240, 1913, 2), (7, 200, 2500, 3),
+    (2, 9, 511, 2), (2, 9, 512, 3), (4, 30, 255, 2), (4, 30, 256, 3)])
 def test_split(p, nc, ns, dim, shuffle):
     cb = W.curve_batch(seed=p * ns + nc, B=3, p=p, nc=nc, ns=ns, dim=dim, shared_u=False, shuffle=shuffle, repeat=0.1)
     run_case(cb, derivs=False)
