@@ -130,8 +130,10 @@ int nurbs_ctx_set_knot_sigma(nurbs_ctx *ctx, float sigma);
 /* Tiling of later calls on this context: the target number of sample points
  * per forward / backward tile (a tile is one wave over <= 64 sample columns
  * and as many rows as reach the target; 0 restores the default: backward
- * tiles of about 72 sample rows, forward tiles of 8 to 64 rows by the size of the
- * batch, which no result depends on).
+ * tiles of about 72 sample rows, or longer where the grid is narrow or the
+ * slots of the tiles would outgrow the points (by the surface's shape alone),
+ * forward tiles of 8 to 64 rows by the size of the batch, which no result
+ * depends on).
  * Results stay bitwise reproducible for a given tiling; different tilings
  * change the summation order of the backward within the tolerances.  An
  * autotuner picks these per workload. */
@@ -311,7 +313,10 @@ int nurbs_surface_uv_fwd(nurbs_ctx *ctx, int B, int p, int q, int nu_c, int nv_c
  * multiple of 2^-s (2^s the largest power of two with npts times the largest
  * term of that gradient tensor at most 2^62) and summed as 64-bit integers,
  * which adds at most npts * max|term| * 2^-63 per entry.  Both are bitwise
- * reproducible, without float atomics, and independent of the batch. */
+ * reproducible, without float atomics, and independent of the batch.
+ * A NaN or infinity in dL/dS reaches the control points and knots of its cell
+ * where pairs are ordered; the exact sums have no such value, and what it
+ * leaves in them is not specified (a NaN term adds nothing). */
 int nurbs_surface_uv_bwd(nurbs_ctx *ctx, int B, int p, int q, int nu_c, int nv_c,
                          const float *ctrl, const float *w, const float *ku,
                          const float *kv, int npts, const float *uv, int uv_shared,
@@ -349,7 +354,9 @@ int nurbs_curve_fwd(nurbs_ctx *ctx, int B, int p, int nc, int dim, const float *
  * grad_mask bits NURBS_GRAD_CTRL, NURBS_GRAD_W and NURBS_GRAD_KU (the knot
  * vector); NURBS_GRAD_KV is rejected.  Outputs as for the surfaces:
  * grad_ctrl [B][nc][dim], grad_w [B][nc], grad_knots [B][nc+p+1], each
- * overwritten when its bit is set.  Deterministic (no atomics). */
+ * overwritten when its bit is set.  Deterministic (no atomics).  A NaN or
+ * infinity in dL/dC reaches the control points and knots of its sample's span
+ * and no others, sorted parameters or not. */
 int nurbs_curve_bwd(nurbs_ctx *ctx, int B, int p, int nc, int dim, const float *ctrl,
                     const float *w, const float *knots, int ns, const float *us,
                     int u_shared, const float *grad_pts, float *grad_ctrl,
@@ -498,7 +505,9 @@ int nurbs_read_device_error(const void *ws, void *stream, int *code);
  * arena of slot_bytes and pinned host buffer of slot_bytes, so up to n_slots
  * batches are in flight.  A request's result does not depend on the other
  * requests of its batch, bit for bit (the plan's tiles follow each surface's
- * own shape, 16384 points to a tile).
+ * own shape, 16384 points to a tile: the least workspace, so that the most
+ * requests fit a slot).  Its gradients are bit for bit those of a call with
+ * nurbs_ctx_set_tiling(ctx, 16384, 16384), which is not the default tiling.
  * ---------------------------------------------------------------------- */
 typedef struct nurbs_server nurbs_server;
 

@@ -29,7 +29,9 @@ ABI), which runs the serving loop in two threads of its own:
 
 Python only submits (one call per request) and waits.  Every result is the
 same alone and in any mix: a plan's tiles depend only on each surface's own
-shape, and every reduction runs in a fixed order.
+shape, and every reduction runs in a fixed order.  The tiles are of 16384
+points (the least workspace per request), so a served gradient has the bits of a
+call on a context with ``set_tiling(16384, 16384)``, not of the default one.
 
 ``PlainServer`` is the per-request baseline: one request at a time through
 the uniform-batch calls.

@@ -60,3 +60,25 @@ def test_infinity_at_the_last_sample_of_every_span(p, nc, ns, dim, shuffle):
     # every basis function is positive strictly inside its spans
     assert np.isposinf(gc[..., 0]).all()
     assert np.isfinite(gc[..., 1:]).all()
+
+
+def test_pairs_ordered_by_cell():
+    # enough pairs to a cell that they are ordered: a NaN reaches its own cell
+    p, q, nu_c, nv_c = 3, 2, 10, 9
+    ub = W.uv_batch(seed=2, B=2, p=p, q=q, nu_c=nu_c, nv_c=nv_c, npts=40 * 7 * 7)
+    args = [T(x) for x in (ub.ctrl, ub.w, ub.ku, ub.kv)]
+    g = ub.upstream.copy()
+    g[0, 100, 1] = np.nan
+    clean, bad = ([x.cpu().numpy() for x in nd.api.surface_uv_bwd(*args, p, q, T(ub.uv), T(u))]
+                  for u in (ub.upstream, g))
+    ku, kv = (int(spans_of(U[0], ub.uv[0, 100:101, i], d)[0]) for i, (U, d) in enumerate(((ub.ku, p), (ub.kv, q))))
+    own = np.zeros((nu_c, nv_c), bool)
+    own[ku - p:ku + 1, kv - q:kv + 1] = True
+    knots = []
+    for n, k, d in ((nu_c + p + 1, ku, p), (nv_c + q + 1, kv, q)):
+        own_k = np.zeros(n, bool)
+        own_k[k - d + 1:k + d + 1] = True
+        knots.append(own_k)
+    for x, y, mine in zip(clean, bad, (own, own, *knots)):
+        assert np.array_equal(x[1], y[1]) and np.array_equal(x[0][~mine], y[0][~mine])
+        assert np.isnan(y[0][mine]).any()
