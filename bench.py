@@ -4,9 +4,9 @@
 Workload (default): the uneven batch -- 4096 surfaces, degrees p, q in 1..5,
 control sides 4..48 and sample sides 16..256 (log-uniform), non-uniform
 clamped knots with 10% repeated interior knots -- run as one ragged plan:
-one persistent forward launch, one persistent backward launch, its
-persistent gather (the v-contraction of the tile accumulators on the matrix
-cores) and the per-surface finalize.  A step is forward + backward (all four gradients)
+one forward launch, one backward launch, its gather (the v-contraction of the
+tile accumulators on the matrix cores) and the finalize of each surface's
+parts.  A step is forward + backward (all four gradients)
 over the whole batch with every input resident in HBM; the upstream
 gradient dL/dS is a fixed synthetic array (see workloads.uneven_batch).
 

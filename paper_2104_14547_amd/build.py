@@ -1,7 +1,7 @@
 """Build libnurbsdiff.so in-tree with hipcc for gfx950.
 
 Each ``csrc/*.hip`` translation unit (one per degree in u for the uniform
-kernels, one per kind and degree class for the persistent kernels, the host
+kernels, one per kind and degree class for the plan kernels, the host
 ABI) is compiled in parallel and linked into one shared library.  The
 per-request serving binding ``csrc/serve_py.c`` (CPython C API, host code
 only) is compiled with the host C compiler into ``_serve_py``.

@@ -22,7 +22,7 @@ struct nurbs_ctx {
     int device = 0;
     unsigned flags = 0;
     int num_cus = 0;
-    int occ[2][2] = {{0, 0}, {0, 0}};  // persistent-kernel workgroups per CU: [class d5, d7][fwd, bwd]
+    int occ[2][2] = {{0, 0}, {0, 0}};  // plan-kernel workgroups that fit a CU: [class d5, d7][fwd, bwd]
     int fwd_tile_pts = 0;              // target points per forward / backward tile (0: the default)
     int bwd_tile_pts = 0;
     int schedule = NURBS_SCHED_STATIC;  // of plans created on this context
@@ -49,7 +49,7 @@ struct nurbs_plan {
     int grid_fwd = 0, grid_bwd = 0;
     size_t ws_bytes = 0;
     int max_nU = 0, max_nV = 0;
-    int maxd = 5;  // degree class of the persistent kernels (5 or 7)
+    int maxd = 5;  // degree class of the plan kernels (5 or 7)
     int schedule = NURBS_SCHED_STATIC;
     std::vector<char> staging;  // host copy of the tables (plans made in caller memory)
     // tracing: event ring per direction (2 events per forward, 4 per backward)
@@ -125,9 +125,9 @@ constexpr size_t kNoAllocScratchBytes = size_t(64) << 20;  // the built-in scrat
 // its batch nor on the kind of call, so the rule looks at its shape alone.  A
 // tile's rows run one after the other (about 0.45 us each), so the longest
 // tile bounds a small batch; more tiles cost a full chip a set-up and p + 1
-// more flushed control rows each.  Forward and backward of
-// uneven batches of n surfaces, kernel time in us by rows per tile (equal
-// parts; the last column 16384 points, up to 256 rows and more):
+// more flushed control rows each.  Forward and backward of uneven batches of n
+// surfaces, kernel time in us by rows per tile (equal parts; the last column
+// 16384 points, up to 256 rows and more):
 //   n       48    56    64    72    80    96   256
 //   4096   488   465   467   460   467   474   465
 //   1024   171   179   184   183   197   211   271
@@ -137,17 +137,19 @@ constexpr size_t kNoAllocScratchBytes = size_t(64) << 20;  // the built-in scrat
 // bicubic 512 x 512 surface: 49 at 64 rows, 134 at 256.
 //
 // Grids of up to kNarrow columns move few points per slot, so their tiles are
-// longer, up to kNarrowRows: 4096 bicubic surfaces of 256 x 3 samples on 10 x 10 nets 285 us a
-// backward at 64 rows, 261 at 128 and at 256.  With more columns 72 rows lose
-// nothing to longer tiles on a full chip (64 of 4096 x 8 on 48 x 48: 135 us at
-// 64 and at 128 rows, 173 at 256), and short ones gain elsewhere (one of those:
-// 85, 111, 162).
+// longer, up to kNarrowRows: 4096 bicubic surfaces of 256 x 3 samples on 10 x 10
+// nets 285 us a backward at 64 rows, 261 at 128 and at 256.  With more columns
+// 72 rows lose nothing to longer tiles on a full chip (64 of 4096 x 8 on 48 x
+// 48: 135 us at 64 and at 128 rows, 173 at 256), and short ones gain elsewhere
+// (one of those: 85, 111, 162).
 //
 // Every tile has a slot that holds a whole net, so the slots of a surface have
 // a budget: kSlotShare times its points' bytes and a MiB, at most the built-in
 // scratch, or what tiles of 16384 points take where that is more.  A surface
 // whose parts exceed it takes fewer and longer ones (one of 100000 x 1 samples
-// on a 16 x 16 net: 20 MB of slots instead of 30).
+// on a 16 x 16 net: 20 MB of slots instead of 30; one of 2048 x 2048 on a 64 x 64
+// net: 64 MB instead of 121, 128 us a backward instead of 106, 513 with tiles
+// of 16384 points).
 constexpr int kDefaultRows = 72, kNarrowRows = 128, kNarrow = 4;
 constexpr size_t kSlotShare = 16;
 
@@ -279,9 +281,8 @@ struct UniformGeom {
 
 // Rows of a forward tile when the caller set none.  A point's bits do not
 // depend on the tile it is in, so the rows may follow the batch: enough tiles
-// to give every SIMD four waves, 8 to 64 rows
-// each (a tile's set-up and first window cost about four rows).  One bicubic
-// 512 x 512 surface, 64 x 64 net: 8 rows 6.8 us, 256 rows 46 us; 256 surfaces
+// to give every SIMD four waves, 8 to 64 rows each (a tile's set-up and first
+// window cost about four rows).  One bicubic 512 x 512 surface, 64 x 64 net: 8 rows 6.8 us, 256 rows 46 us; 256 surfaces
 // of 128 x 128: 16 rows 13.6 us, 64 rows 17.5, 128 rows 26; 1024 of 64 x 64:
 // 16 rows 13.4 us, 64 rows 15.4.
 int auto_rows_fwd(int cus, long long col_rows, int nu_s) {

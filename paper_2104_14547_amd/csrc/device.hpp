@@ -6,8 +6,9 @@
 // helpers.  Everything runs in FP32 on FP32 inputs: span search compares the
 // input values exactly; every factor of the basis recursion and of its knot
 // derivative is a ratio of differences of input values, so each carries a
-// few ulp of relative error.  Only the per-knot sums of the knot gradient
-// (long sums over samples) accumulate in FP64.
+// few ulp of relative error.  Sums over samples are FP32, except the grids'
+// per-knot sums and the scattered pairs' sums over a cell, which are FP64 or
+// exact integers.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>

@@ -432,15 +432,17 @@ __device__ __forceinline__ void seg_scan_select(float4 (&c)[P1], float (&g)[K], 
 }
 
 // What bounds it: VALU issue of the per-sample work (basis, curve point,
-// adjoint): about 150 instructions a step, 7.0e7 wave instructions (113 us of
+// adjoint): about 150 instructions a step, 7.2e7 wave instructions (117 us of
 // issue) for 16384 cubic space curves of 32 control points x 1024 samples,
-// 150 us in all.  One sample per lane with a wave-wide scan and LDS adds for
+// 152 us in all.  One sample per lane with a wave-wide scan and LDS adds for
 // every 64 samples, a search per sample and the adjoint's reciprocals taken
 // twice took 270-300 us.  Items of a lane's own consecutive samples, so that
 // its reads lie hundreds of bytes from its neighbours': 155 us (at degree 1,
 // 64 control points, 4096 x 4096 samples 285 us a pass against 160); dL/dC
-// staged in LDS: 189 us (fewer workgroups resident).  Parameters in random
-// order (4096 quartic curves x 1000 samples): 847 -> 112 us a pass.
+// staged in LDS: 189 us (fewer workgroups resident).  A loop that ends by a
+// vote of the lanes instead of the wave's longest item, counted before it: 240
+// us a pass against 204.  Parameters in random order (4096 quartic curves x
+// 1000 samples): 847 -> 112 us a pass.
 // Degree 5 is held to three waves per SIMD (168 registers, no spills; 181 and two
 // waves otherwise): 16384 curves of 32 control points x 1024 samples 262 -> 218 us.
 template <int P, int DIM, int W>

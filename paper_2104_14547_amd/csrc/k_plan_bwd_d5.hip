@@ -1,4 +1,4 @@
-// Persistent ragged-batch bwd kernel, degrees <= 5.
+// Ragged-batch bwd kernel, degrees <= 5.
 #define ND_MAXD 5
 #define ND_KIND 1
 #include "k_plan.inc"

@@ -1,4 +1,4 @@
-// Persistent ragged-batch fwd kernel, degrees <= 5.
+// Ragged-batch fwd kernel, degrees <= 5.
 #define ND_MAXD 5
 #define ND_KIND 0
 #include "k_plan.inc"

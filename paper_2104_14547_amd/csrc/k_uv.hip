@@ -17,10 +17,11 @@
 // pairs anywhere in the input.  Where the cells of the net hold enough pairs
 // on average the pairs are ordered by cell first (k_uv_cells.hip, which says
 // where the line lies).  Fewer pairs, nets of more cells than that ordering
-// counts in LDS, and workspaces too small for its tables take the path here.  Terms are
-// summed exactly instead of in a fixed order: k_uv_max finds, per surface and gradient tensor, the largest
-// magnitude of a single term; k_uv_acc recomputes every term, rounds it to a
-// multiple of 2^-s, with 2^s chosen so that npts times the largest term
+// counts in LDS, and workspaces too small for its tables take the path here.
+// Terms are summed exactly instead of in a fixed order: k_uv_max finds, per
+// surface and gradient tensor, the largest magnitude of a single term; k_uv_acc
+// recomputes every term, rounds it to a multiple of 2^-s, with 2^s chosen so
+// that npts times the largest term
 // stays below 2^62, and adds it as a 64-bit integer (LDS atomics into a
 // per-workgroup copy of the surface's accumulators when they fit in 58 KiB,
 // then one global atomic per non-zero entry; global atomics otherwise).

@@ -23,15 +23,16 @@
 // M are on the matrix cores in FP64 (v_mfma_f64_4x4x4, 16 to a wave's 64
 // bicubic pairs), where the atomic path has 80 64-bit LDS atomics a pair, as
 // many conversions and a second evaluation of every term.  Measured, forward
-// and backward: 64 bicubic 16 x 16 surfaces x 65536 pairs 242 us (atomic path
-// 586 us), of them k_uv_cell 125, k_uv_order 34, k_uv_sum 19, k_uv_hist 16,
-// k_uv_scan 10, the forward 47; one surface of degree (4, 5), 48 x 41 net,
-// 50001 pairs 140 us (1.78 ms, its accumulators did not fit in LDS).  With M
-// summed on the VALU (one output per lane) k_uv_cell took 138 us, without the
-// next pairs' loads in flight 144; k_uv_sum 37 us with one thread to a control
-// point's value; k_uv_hist and k_uv_scan 18 and 13 us with 128 chunks to a
-// surface instead of 64.  Largest error against 64 bits 2.3e-7 and 1.6e-7
-// (5.9e-7 and 6.8e-7).
+// and backward: 64 bicubic 16 x 16 surfaces x 65536 pairs 238 us (atomic path
+// 585 us), of them k_uv_cell 125, k_uv_order 33, k_uv_hist 16, k_uv_sum 13,
+// k_uv_scan 9, the forward 48; one surface of degree (4, 5), 48 x 41 net, 50001
+// pairs 122 to 140 us, most of it the host (1.81 ms, its accumulators did not
+// fit in LDS).  With M summed on the VALU (one output per lane) k_uv_cell took
+// 138 us, without the next pairs' loads in flight 144; k_uv_sum 37 us with one
+// thread to a control point's value, 19 with one item's load in flight;
+// k_uv_hist and k_uv_scan 18 and 13 us with 128 chunks to a surface instead of
+// 64.  Largest relative error (2-norm) of a gradient against 64 bits, on the
+// same inputs: 1.9e-7 and 1.7e-7 (atomic path 5.9e-7 and 5.7e-7).
 #include "device.hpp"
 #include "launch.hpp"
 #include "../../include/nurbsdiff.h"
